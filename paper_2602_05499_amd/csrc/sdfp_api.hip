@@ -43,7 +43,7 @@ enum StepState { PH_INIT = 0, PH_READY, PH_DRAFTED, PH_VERIFIED, PH_ACCEPTED };
 
 struct Carve {   // byte offsets inside the workspace
     size_t state, out_tokens, prompt, cosT, sinT, acts, part_o, part_ml, counters, zq, zp, head_val, head_idx,
-        prog_target, prog_draft, prog_head, bar, trace, guard_rec, total;
+        prog_target, prog_draft, prog_head, bar, sel, trace, guard_rec, total;
     size_t act_h, act_q, act_a;   // bytes of one residual / query / feed-forward activation block
     size_t acts_bytes;            // bytes of the activation region (also the scratch of the matrix-matrix prompt path)
 };
@@ -182,7 +182,7 @@ Carve carve(const sd_config* c, bool compact = false) {
     k.acts = take(k.acts_bytes);
     k.part_o = take(sizeof(float) * (size_t)n_splits(c) * MAX_ROWS * dq);
     k.part_ml = take(sizeof(float) * (size_t)n_splits(c) * MAX_ROWS * c->n_heads * 2);
-    k.counters = take(sizeof(unsigned) * (size_t)c->n_kv_heads);
+    k.counters = take(sizeof(unsigned) * ((size_t)c->n_kv_heads + 1));   // split merges, and the selection kernels' arrivals
     k.zq = take(sizeof(float) * (size_t)(c->max_k > 0 ? c->max_k : 1) * c->vocab);
     k.zp = take(sizeof(float) * (size_t)(c->max_k + 1) * c->vocab);
     k.head_val = take(sizeof(float) * HEAD_GRID_MAX * MAX_ROWS);
@@ -191,6 +191,7 @@ Carve carve(const sd_config* c, bool compact = false) {
     k.prog_draft = take(sizeof(Phase) * prog_len(c));
     k.prog_head = take(sizeof(Phase) * 2);   // the output head alone, for the prompt's last row (matrix-matrix prompt path)
     k.bar = take(BAR_WORDS * sizeof(unsigned));
+    k.sel = take(sel_buf_bytes());
     k.trace = take(sizeof(unsigned long long) * (TRACE_CAP + 1));
     k.guard_rec = take(sizeof(unsigned long long) * 32);
     k.total = off;
@@ -238,6 +239,15 @@ struct sd_ctx {
     int* out_tokens() const { return reinterpret_cast<int*>(ws + cv.out_tokens); }
     int* prompt() const { return reinterpret_cast<int*>(ws + cv.prompt); }
     float* f(size_t off) const { return reinterpret_cast<float*>(ws + off); }
+    SelBuf sel() const {
+        SelBuf b;
+        b.sum = reinterpret_cast<double*>(ws + cv.sel);
+        b.wres = b.sum + (size_t)SEL_ROWS * SEL_CHUNKS;
+        b.wp = b.wres + SEL_CHUNKS;
+        b.mx = reinterpret_cast<float*>(b.wp + SEL_CHUNKS);
+        b.counter = reinterpret_cast<unsigned*>(ws + cv.counters) + cfg.n_kv_heads;
+        return b;
+    }
 };
 
 // ---- the workspace of contexts made by sd_init_static: device memory that belongs to the library image ------------
@@ -434,7 +444,7 @@ int lazy_device_init(sd_ctx* c) {
     z.max_out = g.max_out;
     HIPCHK(c, hipMemcpyAsync(c->st(), &z, sizeof(z), hipMemcpyHostToDevice, c->stream));
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(256), 0, c->stream,
-                       reinterpret_cast<unsigned*>(c->ws + c->cv.counters), g.n_kv_heads);
+                       reinterpret_cast<unsigned*>(c->ws + c->cv.counters), g.n_kv_heads + 1);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.bar), BAR_WORDS);
     // the diagnostics' records start empty whatever the workspace held before
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream,
@@ -761,6 +771,13 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
     return forward<bf16_t>(c, Rows{1, ROWS_VERIFY, 0}, PROG_HEAD, hp);
 }
 
+// one inverse-CDF draw from a row of logits into st->d[off] / st->amax[off]
+void pick_sample(sd_ctx* c, const float* z, float u, int dst, int off) {
+    const int V = c->cfg.vocab, len = sel_chunk_len(V);
+    hipLaunchKernelGGL(k_pick_sample, dim3((V + len - 1) / len), dim3(SEL_THREADS), 0, c->stream, z, V, len, c->cfg.temperature, u,
+                       c->sel(), c->st(), dst, off);
+}
+
 template <typename WT>
 int do_prefill(sd_ctx* c, const int32_t* prompt_host, int n, int mode, const float* u_host) {
     int e = lazy_device_init(c);
@@ -770,7 +787,7 @@ int do_prefill(sd_ctx* c, const int32_t* prompt_host, int n, int mode, const flo
     // a fresh sequence starts from clean barrier and split-merge counters (also the way out of SD_ETIMEOUT)
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.bar), BAR_WORDS);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.counters),
-                       c->cfg.n_kv_heads);
+                       c->cfg.n_kv_heads + 1);
     const bool keep = mode == SD_SAMPLE || c->keep_logits;
     const bool gemm = std::is_same<WT, bf16_t>::value && c->panel.P > 0 &&
                       (c->prefill_mode == 1 || (c->prefill_mode < 0 && n >= PREFILL_MATRIX_MIN_ROWS));
@@ -786,9 +803,7 @@ int do_prefill(sd_ctx* c, const int32_t* prompt_host, int n, int mode, const flo
             if ((e = forward<WT>(c, rows, PROG_TARGET, hp))) return e;
         }
     }
-    if (mode == SD_SAMPLE)
-        hipLaunchKernelGGL(k_pick_sample, dim3(1), dim3(1024), 0, c->stream, c->f(c->cv.zp), c->cfg.vocab,
-                           c->cfg.temperature, u_host[0], c->st(), (int)ROWS_VERIFY, 0);
+    if (mode == SD_SAMPLE) pick_sample(c, c->f(c->cv.zp), u_host[0], (int)ROWS_VERIFY, 0);
     hipLaunchKernelGGL(k_commit_first, dim3(1), dim3(64), 0, c->stream, c->st(), c->out_tokens(), n);
     HIPCHK(c, hipGetLastError());
     return SD_OK;
@@ -803,10 +818,7 @@ int do_draft(sd_ctx* c, int K, int mode, const float* u_host) {
         HeadPlan hp{true, 0, keep ? c->f(c->cv.zq) + (size_t)i * c->cfg.vocab : nullptr, ROWS_DRAFT, i};
         int e = forward<WT>(c, rows, PROG_DRAFT, hp);
         if (e) return e;
-        if (mode == SD_SAMPLE)
-            hipLaunchKernelGGL(k_pick_sample, dim3(1), dim3(1024), 0, c->stream,
-                               c->f(c->cv.zq) + (size_t)i * c->cfg.vocab, c->cfg.vocab, c->cfg.temperature, u_host[i],
-                               c->st(), (int)ROWS_DRAFT, i);
+        if (mode == SD_SAMPLE) pick_sample(c, c->f(c->cv.zq) + (size_t)i * c->cfg.vocab, u_host[i], (int)ROWS_DRAFT, i);
     }
     HIPCHK(c, hipGetLastError());
     return SD_OK;
@@ -827,8 +839,11 @@ int do_accept(sd_ctx* c, int mode, const float* u_host) {
         Uni un;
         std::memset(&un, 0, sizeof(un));
         for (int i = 0; i <= c->K_cur; ++i) un.u[i] = u_host[i];
-        hipLaunchKernelGGL(k_accept_sample, dim3(1), dim3(1024), 0, c->stream, c->f(c->cv.zq), c->f(c->cv.zp),
-                           c->cfg.vocab, c->cfg.temperature, un, c->st(), c->out_tokens());
+        const int V = c->cfg.vocab, len = sel_chunk_len(V), chunks = (V + len - 1) / len;
+        hipLaunchKernelGGL(k_sel_stats, dim3(chunks, 2 * c->K_cur + 1), dim3(SEL_THREADS), 0, c->stream, c->f(c->cv.zq),
+                           c->f(c->cv.zp), V, len, c->cfg.temperature, c->K_cur, c->sel());
+        hipLaunchKernelGGL(k_accept_sample, dim3(chunks), dim3(SEL_THREADS), 0, c->stream, c->f(c->cv.zq), c->f(c->cv.zp), V, len,
+                           c->cfg.temperature, c->K_cur, un, c->sel(), c->st(), c->out_tokens());
     }
     HIPCHK(c, hipGetLastError());
     return SD_OK;
