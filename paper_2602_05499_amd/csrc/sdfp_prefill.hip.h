@@ -16,7 +16,8 @@
 //   * norm scale, rotary embedding, SwiGLU, residual add, bfloat16 rounding of keys / values, the sum of squares of a
 //     row and the split of an activation into pieces use the shared helpers of sdfp_common.hip.h, built from single
 //     float32 operations that the compiler cannot contract with their neighbours;
-//   * attention runs the decode kernels' own attn_split on 16-row chunks.
+//   * attention runs the decode kernels' own attn_split on 16-row chunks, or its operations on the matrix cores
+//     (k_pf_attn_mx).
 // The GEMM therefore walks the reduction dimension share by share (a permutation of the usual order), which costs
 // nothing: every step of it is still a whole 64-byte line of 16 weight rows.
 //
@@ -25,6 +26,7 @@
 // matrix-core step -- 16 rows x 64 bytes -- is one contiguous kilobyte, lane l's 16 bytes at l * 16, so that the GEMM
 // stages a slab with contiguous reads and writes it to LDS as it comes; q, att [P][H*hd] float32; rs [P] float32.
 #pragma once
+#include <type_traits>
 #include "sdfp_attn.hip.h"
 
 namespace sdfp {
@@ -587,6 +589,360 @@ __global__ __launch_bounds__(WG_THREADS, 4) void k_pf_attn(PfAttn a) {   // 4 wa
             attn_split<bf16_t, LPP, 0, true, LONGCTX>(a.kc, a.vc, aa, reinterpret_cast<float*>(lds), split, g);
             __syncthreads();
         }
+    }
+}
+
+// ---- the same attention on the float32 matrix cores (head_dim 64 and 128).  v_mfma_f32_16x16x4_f32 computes every output
+// as a chain of four fused multiply-adds in ascending k, each correctly rounded (measured on 2 million products, wide
+// exponents and denormals among them: no bit differs), so it can run attn_split's own operations:
+//   scores   one instruction with C = 0 forms the 4-dim partial products of 16 keys x 16 queries; the tree of
+//            group_sum_dpp over the hd / 4 partial products is plain register adds;
+//   values   the chain of an output over a wave's positions, per position slot, is NL / 4 instructions; the slots' tree and
+//            the sum over the decode kernels' waves, in their order, are plain register adds.
+// A wave owns a tile of 16 prompt rows x one query head; the scores of a tile land on the lanes in the operand order of
+// the value products (key rows of a tile are dealt to make it so), so probabilities never leave the registers and
+// nothing crosses lanes but the soft-max statistics.
+// What bounds it: per tile and split of 128 positions 512 instructions (head_dim 128) that hold a matrix core 32 cycles
+// each, and 2700 vector instructions of 4.  Counters at 4096 positions: matrix cores 48 % busy, vector issue 38 %, the rest
+// barriers and staging.  Measured against k_pf_attn on the vector ALUs: 8 KV heads x 4 queries, 512 rows at 3584-4096
+// positions 1740 -> 475 us (the 4096-token prompt 429 -> 244 ms); 32 heads, 512 rows 122 -> 70 us.
+//
+// Positions.  attn_split walks position j = l * NC + ch, NC = 8 waves x PPL slots, chain ch = wave * PPL + slot over
+// l = 0 .. NL - 1.  Here lane group gq = lane / 16 holds l = gq + 4 i, i < NI = NL / 4, of every chain: unit
+// u = ch * NI + i (0..31) of group gq is position (gq + 4 i) * NC + ch.
+//
+// Workgroup: 4 tiles of one KV head (consecutive in (chunk, query head) order) x 2 splits at a time: waves 0-3 take the
+// even splits, waves 4-7 the odd ones, each half stages its split's keys and values in LDS in operand order; the next
+// pair is loaded into registers meanwhile.  Split partials go to a slot of scratch memory of the workgroup's own and are
+// merged at the end, as attn_split does, by the same operations in ascending split order.
+struct PfAttnMx {
+    const float* q;        // [P][H*hd] of the panel
+    float* att;            // [P][H*hd]
+    const bf16_t *kc, *vc; // this layer's planes
+    float* part;           // one slot per workgroup: [n_slots][64][hd] partials, then [n_slots][64][2] statistics
+    size_t part_stride;    // floats per slot
+    size_t part_ml_off;    // floats from a slot's start to its statistics
+    int M, pos0;           // valid rows of the panel, absolute position of row 0
+    LayerDims L;
+};
+constexpr int PFX_TILES = 4;                       // query tiles per workgroup
+constexpr int PFX_QUERIES = PFX_TILES * 16;
+__host__ __device__ constexpr size_t pfx_lds_bytes(int hd) { return (size_t)2 * 2 * ATT_SL * hd * 2; }   // 2 splits x (K, V)
+__host__ __device__ constexpr size_t pfx_slot_floats(int hd, int n_splits) { return (size_t)n_splits * PFX_QUERIES * (hd + 2); }
+
+__device__ __forceinline__ f32x4 add4_rn(const f32x4& a, const f32x4& b) {
+    return f32x4{add_rn(a.x, b.x), add_rn(a.y, b.y), add_rn(a.z, b.z), add_rn(a.w, b.w)};
+}
+// value u (of 8 packed bfloat16) of an operand quad, widened
+__device__ __forceinline__ float bf16_of8(const u32x4& r, int u) {
+    const unsigned w = u < 2 ? r.x : (u < 4 ? r.y : (u < 6 ? r.z : r.w));
+    return __uint_as_float((u & 1) ? (w & 0xFFFF0000u) : (w << 16));
+}
+// lower halves (hi = false) or upper halves of two words, a's first
+__device__ __forceinline__ unsigned pack_halves(unsigned a, unsigned b, bool hi) {
+    return __builtin_amdgcn_perm(b, a, hi ? 0x07060302u : 0x05040100u);
+}
+// x + y' where lanes 0-31 get x of their own and of lane + 32, lanes 32-63 y of both (and the same by 16-lane rows)
+__device__ __forceinline__ float fold32(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return add_rn(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float fold16(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return add_rn(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <int LPP>
+__global__ __launch_bounds__(WG_THREADS, 2) void k_pf_attn_mx(PfAttnMx a) {
+    constexpr int HD = LPP * 4, PPL = 64 / LPP, NC = NWAVE * PPL, NL = ATT_SL / NC, NI = NL / 4;
+    constexpr int GQ = HD / 32;            // 16-byte fragments per lane of a key tile (8 4-dim groups each)
+    constexpr int DT = HD / 16;            // 16-dim tiles of the output
+    constexpr int DQ = HD / 4;             // 4-dim quads of a value row
+    constexpr int NU = HD / 64;            // staging units per thread, of keys and of values
+    static_assert(NI >= 1 && NC * NI == 32 && NWAVE == 8 && ATT_SL == 128, "32 units per lane group");
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, gq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tl = wave & 3, sp = wave >> 2, ht = tid & 255;
+    const int H = a.L.H, Hkv = a.L.Hkv, grp = H / Hkv;
+    const int n_chunks = (a.M + 15) >> 4, n_tk = n_chunks * grp, n_tg = (n_tk + PFX_TILES - 1) / PFX_TILES;
+    const float scale = 1.0f / sqrtf((float)HD);
+    char* const kb = lds + sp * (2 * ATT_SL * HD * 2);
+    char* const vb = kb + ATT_SL * HD * 2;
+    float* const slot = a.part + (size_t)blockIdx.x * a.part_stride;
+    float* const slot_ml = slot + a.part_ml_off;
+    auto pos_of = [](int u, int g) { return (g + 4 * (u % NI)) * NC + u / NI; };   // position in its split
+
+    // items: KV head fastest (a head's workgroups share an XCD and its L2 where Hkv is a multiple of 8), longest rows first
+    for (int it = blockIdx.x; it < n_tg * Hkv; it += gridDim.x) {
+        const int g = it % Hkv, tg = n_tg - 1 - it / Hkv;
+        auto chunk_end = [&](int c) { return a.pos0 + min(a.M, c * 16 + 16); };   // positions a chunk's attention covers
+        const int t_last = min(tg * PFX_TILES + PFX_TILES, n_tk) - 1;
+        const int end_wg = chunk_end(t_last / grp);
+        const int n_act_wg = (end_wg + ATT_SL - 1) / ATT_SL;
+        // this wave's tile (a tile past the last one does no work)
+        const int t = tg * PFX_TILES + tl;
+        const bool live = t < n_tk;
+        const int c = min(t, n_tk - 1) / grp, hq = g * grp + min(t, n_tk - 1) % grp;
+        const int end = chunk_end(c), rows = min(16, a.M - c * 16), n_act = (end + ATT_SL - 1) / ATT_SL;
+        const int my_pos = a.pos0 + c * 16 + r16;          // absolute position of this lane's query row
+
+        // the queries, operand B of the score products: lane (row r16, gq) holds dims 4 G + gq
+        float qv[DQ];
+        {
+            const float* qrow = a.q + (size_t)(c * 16 + min(r16, rows - 1)) * H * HD + (size_t)hq * HD + gq;
+#pragma unroll
+            for (int G = 0; G < DQ; ++G) qv[G] = qrow[4 * G];
+        }
+        const char* kp = reinterpret_cast<const char*>(a.kc + (size_t)g * a.L.max_seq * HD);
+        const char* vp = reinterpret_cast<const char*>(a.vc + (size_t)g * a.L.max_seq * HD);
+        u32x4 kr[NU][4];
+        u32x2 vr[NU][8];
+        // loads are unconditional, addresses clamped to the last row; rows past it are replaced by zeros when they are staged
+        auto fetch = [&](int split) {
+            const int start = min(split, n_act_wg - 1) * ATT_SL, last = min(ATT_SL, end_wg - start) - 1;
+#pragma unroll
+            for (int n = 0; n < NU; ++n) {
+                const int x = ht + 256 * n;
+                const int r = x & 15, G8 = (x >> 4) % GQ, kt = (x >> 4) / GQ;
+                const int j = min(pos_of(kt * 4 + (r & 3), r >> 2), last);
+                const unsigned off = (unsigned)(start + j) * (HD * 2) + G8 * 64;   // (a KV head's plane is far below 4 GB)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) kr[n][w] = *reinterpret_cast<const u32x4*>(kp + (off + w * 16));
+                const int dq = x % DQ, uq = (x / DQ) & 3, gv = x / (DQ * 4);
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    vr[n][k] = *reinterpret_cast<const u32x2*>(vp + ((unsigned)(start + min(pos_of(uq * 8 + k, gv), last)) * (HD * 2) + dq * 8));
+            }
+        };
+        auto stage = [&](int split) {
+            const int start = min(split, n_act_wg - 1) * ATT_SL, npos = min(ATT_SL, end_wg - start);
+#pragma unroll
+            for (int n = 0; n < NU; ++n) {
+                const int x = ht + 256 * n;
+                // keys: fragment (key tile, 8 4-dim groups), lane (row r, gq)'s 16 bytes = dims 4 G + gq of those groups
+                const int r = x & 15, G8 = (x >> 4) % GQ, kt = (x >> 4) / GQ;
+                const bool ok = pos_of(kt * 4 + (r & 3), r >> 2) < npos;
+                unsigned w[16];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { w[4 * e] = kr[n][e].x; w[4 * e + 1] = kr[n][e].y; w[4 * e + 2] = kr[n][e].z; w[4 * e + 3] = kr[n][e].w; }
+#pragma unroll
+                for (int gg = 0; gg < 4; ++gg) {
+                    unsigned o[4];
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) {
+                        o[p] = pack_halves(w[4 * p + (gg >> 1)], w[4 * p + 2 + (gg >> 1)], gg & 1);
+                        o[p] = ok ? o[p] : 0u;
+                    }
+                    *reinterpret_cast<u32x4*>(kb + ((kt * GQ + G8) * 64 + gg * 16 + r) * 16) = u32x4{o[0], o[1], o[2], o[3]};
+                }
+                // values: fragment (16-dim tile, 8 units), lane (dim r, gq)'s 16 bytes = those units' positions; the lanes'
+                // places are XORed with the tile, or the 8 tiles a wave writes at once would share their banks
+                const int dq = x % DQ, uq = (x / DQ) & 3, gv = x / (DQ * 4), dt = dq >> 2;
+                u32x2 v[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const bool vok = pos_of(uq * 8 + k, gv) < npos;
+                    v[k] = u32x2{vok ? vr[n][k].x : 0u, vok ? vr[n][k].y : 0u};
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    unsigned o[4];
+#pragma unroll
+                    for (int p = 0; p < 4; ++p)
+                        o[p] = pack_halves((e >> 1) ? v[2 * p].y : v[2 * p].x, (e >> 1) ? v[2 * p + 1].y : v[2 * p + 1].x, e & 1);
+                    const int place = (gv * 16 + (dq & 3) * 4 + e) ^ (dt & 7);
+                    *reinterpret_cast<u32x4*>(vb + ((dt * 4 + uq) * 64 + place) * 16) = u32x4{o[0], o[1], o[2], o[3]};
+                }
+            }
+        };
+
+        fetch(sp);
+        for (int s0 = 0; s0 < n_act_wg; s0 += 2) {
+            const int split = s0 + sp;
+            __syncthreads();                       // the previous pair (or merge) has been read
+            stage(split);
+            if (s0 + 2 < n_act_wg) fetch(split + 2);   // uniform over the workgroup
+            __syncthreads();
+            if (!live || split >= n_act) continue;     // uniform over the wave
+            const int start = split * ATT_SL, npos = min(ATT_SL, end - start);
+
+            // scores: unit u = kt * 4 + e of this lane's query in s[u].  The instructions of a block (8 4-dim groups of a key
+            // tile) are issued with the tree of the previous block between them: both fit the 32 cycles an instruction
+            // occupies the matrix core, and one wave alone keeps it busy.
+            float s[32];
+            {
+                constexpr int NB = 8 * GQ;   // blocks
+                auto key_frag = [&](int b) { return *reinterpret_cast<const u32x4*>(kb + (b * 64 + lane) * 16); };
+                f32x4 d[2][8], part[GQ];
+                u32x4 kf = key_frag(0);
+#pragma unroll
+                for (int b = 0; b <= NB; ++b) {
+                    if (b < NB) {
+                        const u32x4 kcur = kf;
+                        if (b + 1 < NB) kf = key_frag(b + 1);
+#pragma unroll
+                        for (int G = 0; G < 8; ++G)
+                            d[b & 1][G] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf16_of8(kcur, G), qv[(b % GQ) * 8 + G],
+                                                                              f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    }
+                    if (b > 0) {
+                        f32x4* t = d[(b - 1) & 1];
+#pragma unroll
+                        for (int w = 1; w < 8; w <<= 1)
+#pragma unroll
+                            for (int i = 0; i + w < 8; i += 2 * w) t[i] = add4_rn(t[i], t[i + w]);
+                        const int G8 = (b - 1) % GQ, kt = (b - 1) / GQ;
+                        part[G8] = t[0];
+                        if (G8 == GQ - 1) {
+#pragma unroll
+                            for (int w = 1; w < GQ; w <<= 1)
+#pragma unroll
+                                for (int i = 0; i + w < GQ; i += 2 * w) part[i] = add4_rn(part[i], part[i + w]);
+                            const float pv[4] = {part[0].x, part[0].y, part[0].z, part[0].w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) s[kt * 4 + e] = mul_rn(pv[e], scale);
+                        }
+                    }
+                    if (b < NB) {
+#pragma unroll
+                        for (int G = 0; G < 8; ++G) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // a matrix-core instruction
+                            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // and vector instructions under it
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            const int n_seen = min(npos, my_pos - start + 1);   // positions of the split this lane's query attends to
+            if (start + ATT_SL > a.pos0 + c * 16 + 1 || npos < ATT_SL) {   // uniform: the split reaches the tile's own rows
+#pragma unroll
+                for (int u = 0; u < 32; ++u) s[u] = pos_of(u, gq) < n_seen ? s[u] : -INFINITY;
+            }
+            // soft-max statistics: the maximum, and the sum in wave_sum's order (positions j and j + 64 first, then the
+            // butterfly over 32, 16, .., 1: position bits are i, gq or the chain, highest bit first)
+            float mx = s[0];
+#pragma unroll
+            for (int u = 1; u < 32; ++u) mx = fmaxf(mx, s[u]);
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+#pragma unroll
+            for (int u = 0; u < 32; ++u) s[u] = mx > -INFINITY ? __expf(sub_rn(s[u], mx)) : 0.f;
+            float R[NC / 4];   // R[x] of group gq: chain 4 x + gq, summed over its positions
+#pragma unroll
+            for (int x = 0; x < NC / 4; ++x) {
+                float tt[4];
+#pragma unroll
+                for (int y = 0; y < 4; ++y) tt[y] = NI == 2 ? add_rn(s[(4 * x + y) * NI], s[(4 * x + y) * NI + NI - 1]) : s[4 * x + y];
+                R[x] = fold16(fold32(tt[0], tt[2]), fold32(tt[1], tt[3]));
+            }
+#pragma unroll
+            for (int w = NC / 8; w >= 1; w >>= 1)
+#pragma unroll
+                for (int x = 0; x < w; ++x) R[x] = add_rn(R[x], R[x + w]);
+            float l = R[0];
+            l = add_rn(l, __shfl_xor(l, 32));
+            l = add_rn(l, __shfl_xor(l, 16));
+            if (gq == 0)
+                *reinterpret_cast<float2*>(slot_ml + ((size_t)split * PFX_QUERIES + tl * 16 + r16) * 2) = float2{mx, l};
+
+            // values.  Rows past the tile's own chunk that another tile of the workgroup needed are zeros here, as in
+            // attn_split (their probabilities are 0, but 0 times an infinity would not be)
+            float* po = slot + ((size_t)split * PFX_QUERIES + tl * 16 + r16) * HD + gq * 4;
+            auto values = [&](auto masked) {
+#pragma unroll 2
+                for (int dt = 0; dt < DT; ++dt) {
+                    u32x4 vf[4];
+#pragma unroll
+                    for (int uq = 0; uq < 4; ++uq)
+                        vf[uq] = *reinterpret_cast<const u32x4*>(vb + ((dt * 4 + uq) * 64 + (lane ^ (dt & 7))) * 16);
+                    auto val = [&](int u) {
+                        const float v = bf16_of8(vf[u >> 3], u & 7);
+                        return masked.value && pos_of(u, gq) >= npos ? 0.f : v;
+                    };
+                    // four chains at a time, the previous four folded under them
+                    constexpr int NG = NC / 4;
+                    f32x4 tot = f32x4{0.f, 0.f, 0.f, 0.f}, o[2][4];
+#pragma unroll
+                    for (int q = 0; q <= NG; ++q) {
+                        if (q < NG) {
+#pragma unroll
+                            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                                for (int x = 0; x < 4; ++x) {
+                                    const int u = (q * 4 + x) * NI + i;
+                                    o[q & 1][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                        val(u), s[u], i == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : o[q & 1][x], 0, 0, 0);
+                                }
+                        }
+                        if (q > 0) {
+                            f32x4* t = o[(q - 1) & 1];
+                            if constexpr (PPL == 2) {
+                                tot = add4_rn(tot, add4_rn(t[0], t[1]));
+                                tot = add4_rn(tot, add4_rn(t[2], t[3]));
+                            } else {
+                                static_assert(PPL == 2 || PPL == 4, "slots per wave");
+                                tot = add4_rn(tot, add4_rn(add4_rn(t[0], t[1]), add4_rn(t[2], t[3])));
+                            }
+                        }
+                        if (q < NG) {
+#pragma unroll
+                            for (int x = 0; x < 4 * NI; ++x) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    *reinterpret_cast<f32x4*>(po + dt * 16) = tot;
+                }
+            };
+            if (npos < ATT_SL) values(std::true_type{}); else values(std::false_type{});
+        }
+
+        // merge: the splits' partials weighted by exp(max_s - max) in ascending split order, four outputs per thread.  The
+        // statistics of as many queries as fit go to LDS first.
+        const int qb = min(PFX_QUERIES, max(1, (int)(pfx_lds_bytes(HD) / 8) / n_act_wg));
+        for (int q0 = 0; q0 < PFX_QUERIES; q0 += qb) {
+            const int nqb = min(qb, PFX_QUERIES - q0);
+            float2* stat = reinterpret_cast<float2*>(lds);   // [n_act_wg][qb]
+            __syncthreads();      // also: every wave's partials are written
+            for (int e = tid; e < n_act_wg * nqb; e += WG_THREADS) {
+                const int sI = e / nqb, ql = e - sI * nqb;
+                stat[sI * qb + ql] = *reinterpret_cast<const float2*>(slot_ml + ((size_t)sI * PFX_QUERIES + q0 + ql) * 2);
+            }
+            __syncthreads();
+            for (int e = tid; e < nqb * DQ; e += WG_THREADS) {
+                const int ql = e / DQ, d0 = (e - ql * DQ) * 4, qi = q0 + ql, tq = tg * PFX_TILES + (qi >> 4);
+                if (tq >= n_tk) continue;
+                const int cq = tq / grp, m = cq * 16 + (qi & 15), hqq = g * grp + tq % grp;
+                if (m >= a.M) continue;
+                const int na = (chunk_end(cq) + ATT_SL - 1) / ATT_SL;
+                float gmax = -INFINITY;
+                for (int sI = 0; sI < na; ++sI) gmax = fmaxf(gmax, stat[sI * qb + ql].x);
+                const float* src = slot + (size_t)qi * HD + d0;
+                float num[4] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
+                for (int sb = 0; sb < na; sb += 8) {
+                    f32x4 os[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        os[k] = *reinterpret_cast<const f32x4*>(src + (size_t)min(sb + k, na - 1) * (PFX_QUERIES * HD));
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        if (sb + k < na) {
+                            const float2 ml = stat[(sb + k) * qb + ql];
+                            const float w = (ml.x > -INFINITY) ? __expf(ml.x - gmax) : 0.f;
+                            num[0] = fmaf(w, os[k].x, num[0]); num[1] = fmaf(w, os[k].y, num[1]);
+                            num[2] = fmaf(w, os[k].z, num[2]); num[3] = fmaf(w, os[k].w, num[3]);
+                            den = fmaf(w, ml.y, den);
+                        }
+                    }
+                }
+                *reinterpret_cast<f32x4*>(a.att + (size_t)m * H * HD + (size_t)hqq * HD + d0) =
+                    f32x4{num[0] / den, num[1] / den, num[2] / den, num[3] / den};
+            }
+        }
+        __syncthreads();   // the statistics have been read before the next item's keys overwrite them
     }
 }
 

@@ -166,6 +166,27 @@ def test_matrix_prompt_path_panel_boundaries(gpu, small_shapes):
     _both_paths(gpu, s, [511, 512, 513, 1100])
 
 
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("heads,kv_heads,head_dim,lengths", [
+    (3, 1, 64, [100, 128, 129, 257, 400]),          # tiles of a workgroup in different 16-row chunks, a tile group not full
+    (4, 4, 64, [127, 128, 129, 130, 256, 257]),     # plain heads: vector-ALU kernel within one split, matrix cores beyond
+    (8, 1, 128, [16, 17, 129, 1024, 1025]),         # more query heads than tiles of a workgroup; more than 8 splits
+    (5, 5, 128, [513, 640, 1100]),                  # several panels; a tile group that ends inside a split
+])
+def test_panel_attention_tile_edges(gpu, heads, kv_heads, head_dim, lengths):
+    """Panel attention around the edges of a split (128 positions), a 16-row chunk, a workgroup's four tiles and a panel."""
+    s = synth.CONFIGS["tiny"].with_(name="edges_bf16", dtype="bf16", n_heads=heads, n_kv_heads=kv_heads, head_dim=head_dim,
+                                    d_ffn=704, gain_std=0.1, init_std=0.05)
+    _both_paths(gpu, s, lengths)
+
+
+@pytest.mark.timeout(600)
+def test_panel_attention_with_fewer_partial_slots_than_items(gpu):
+    """1100 positions of 32 plain heads: 256 items per panel, room for the split partials of 223 workgroups."""
+    s = synth.CONFIGS["7b"].with_(name="7b-1layer", n_layers=1, n_skip=0, gain_std=0.1)
+    _both_paths(gpu, s, [1100])
+
+
 def test_tiled_weights_argument_errors(gpu, small_shapes):
     from synth.device import DeviceWeights
     P = gpu
