@@ -765,7 +765,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
                 hipLaunchKernelGGL(k_pf_residual_norm_split, dim3(np), dim3(WG_THREADS), 0, c->stream, h, (const float*)shares,
                                    a.part_arr, d, g.rms_eps, lp.ffn_norm, rs, xs_a, pf_xs_piece(np, d));
             } else {
-                hipLaunchKernelGGL(k_pf_residual, dim3(512), dim3(256), 0, c->stream, h, shares, a.part_arr, np * d / 4);
+                hipLaunchKernelGGL(k_pf_residual, dim3(512), dim3(256), 0, c->stream, h, h, shares, a.part_arr, np * d / 4);
                 hipLaunchKernelGGL(k_pf_rownorm, dim3(np), dim3(WG_THREADS), 0, c->stream, h, d, g.rms_eps, rs);
                 hipLaunchKernelGGL(k_pf_split, dim3(1024), dim3(256), 0, c->stream, h, lp.ffn_norm, np, d, xs_a, pf_xs_piece(np, d));
             }
@@ -797,7 +797,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             if (e) return e;
             // the down projection's residual update: fused into the next layer's first kernel, or done here
             if (!fused || l == g.n_layers - 1)
-                hipLaunchKernelGGL(k_pf_residual, dim3(512), dim3(256), 0, c->stream, h, shares, a.part_arr, np * d / 4);
+                hipLaunchKernelGGL(k_pf_residual, dim3(512), dim3(256), 0, c->stream, h, h, shares, a.part_arr, np * d / 4);
         }
 #undef SDFP_PF_ONE_TILE
         if (p0 + pl.P >= n)   // the prompt's last row goes to the output head

@@ -155,7 +155,41 @@ __global__ __launch_bounds__(256) void k_fit_bmm(FitBmm p) {
         const int h = bz * p.inner + hh;
         const float* Ah = p.A + (size_t)(h / p.a_div) * p.a_hs;
         const float* Bh = p.B + (size_t)(h / p.b_div) * p.b_hs;
-        for (int k0 = k_lo; k0 < k_hi; k0 += 16) {
+        // Whole steps, operands loaded one step ahead of the instructions that use them (the last step loads itself again,
+        // unused); without that every step waited out the latency of its loads (512 positions, 32 heads of 128: P V 121 us, now
+        // 46; P^T dO 95, now 38).  The ragged end, and operands whose rows
+        // do not allow the 16-byte loads, take the loop below.
+        int k_from = k_lo;
+        if ((AT || va) && (!BT || vb) && k_lo + 16 <= min(k_hi, p.K)) {
+            const int k_full = k_lo + (min(k_hi, p.K) - k_lo) / 16 * 16;
+            f32x4 an, bn4[4];
+            auto load = [&](int k0) {
+                const int kb = k0 + gq * 4;
+                if constexpr (!AT) an = *reinterpret_cast<const f32x4*>(Ah + (size_t)am * p.lda + kb);
+                else an = f32x4{Ah[(size_t)kb * p.lda + am], Ah[(size_t)(kb + 1) * p.lda + am], Ah[(size_t)(kb + 2) * p.lda + am],
+                                Ah[(size_t)(kb + 3) * p.lda + am]};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if constexpr (BT) bn4[c] = *reinterpret_cast<const f32x4*>(Bh + (size_t)bn[c] * p.ldb + kb);
+                    else bn4[c] = f32x4{Bh[(size_t)kb * p.ldb + bn[c]], Bh[(size_t)(kb + 1) * p.ldb + bn[c]],
+                                        Bh[(size_t)(kb + 2) * p.ldb + bn[c]], Bh[(size_t)(kb + 3) * p.ldb + bn[c]]};
+                }
+            };
+            load(k_lo);
+            for (int k0 = k_lo; k0 < k_full; k0 += 16) {
+                const f32x4 a = an;
+                f32x4 b[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) b[c] = bn4[c];
+                load(min(k0 + 16, k_full - 16));
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[c][e], acc[c], 0, 0, 0);
+            }
+            k_from = k_full;
+        }
+        for (int k0 = k_from; k0 < k_hi; k0 += 16) {
             const int kb = k0 + gq * 4;                     // this lane group's four k
             float a[4], b[4][4];
             if (kb + 4 <= p.K) {
@@ -275,24 +309,28 @@ __global__ __launch_bounds__(256) void k_fit_ce(float* __restrict__ z, const int
 // ---- transposed copy of a bfloat16 matrix, written in the tile order of the GEMM's weight operand (pf_tile_weights):
 // the copy is W^T [C][R] of src W [R][C]; its tile t = rows 16 t .. (columns of W), step s = values 32 s .. of a row (rows of
 // W), lane l's 16 bytes = row l % 16 of the tile, values (l / 16) * 8 .. of the step, at l * 16 of the kilobyte
-// (t * R / 32 + s).  One workgroup per 32 x 32 block of W, through LDS.  R a multiple of 32, C of 16. ------------------
+// (t * R / 32 + s).  One workgroup per 32 x 256 block of W, through LDS.  R a multiple of 32, C of 16. ------------------
+constexpr int FIT_TR_COLS = 256;   // columns of W per workgroup: 16-byte reads of whole lines (4096 x 4096: 19 us; with 2-byte reads of a column per thread 44)
 __global__ __launch_bounds__(256) void k_fit_transpose(const bf16_t* __restrict__ src, int R, int C, bf16_t* __restrict__ dst) {
-    __shared__ bf16_t tile[32][33];
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int y = ty; y < 32; y += 8)
-        if (r0 + y < R && c0 + tx < C) tile[y][tx] = src[(size_t)(r0 + y) * C + c0 + tx];
-    __syncthreads();
-    if (threadIdx.x < 128) {   // unit = (column c of W, quarter gq of the step): 8 values W[r0 + gq * 8 ..][c]
-        const int cl = threadIdx.x & 31, gq = threadIdx.x >> 5, c = c0 + cl;
-        if (c < C) {
-            unsigned w[4];
+    __shared__ __attribute__((aligned(16))) bf16_t tile[32][FIT_TR_COLS + 8];
+    const int c0 = blockIdx.x * FIT_TR_COLS, r0 = blockIdx.y * 32;
+    const int cu = (threadIdx.x & 31) * 8;
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                w[e] = (unsigned)tile[gq * 8 + 2 * e][cl] | ((unsigned)tile[gq * 8 + 2 * e + 1][cl] << 16);
-            const size_t frag = (size_t)(c >> 4) * (R >> 5) + (r0 >> 5);
-            *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(dst) + frag * PF_FRAG_BYTES + gq * 256 + (c & 15) * 16) =
-                u32x4{w[0], w[1], w[2], w[3]};
-        }
+    for (int y = threadIdx.x >> 5; y < 32; y += 8)
+        if (r0 + y < R && c0 + cu < C)
+            *reinterpret_cast<u32x4*>(&tile[y][cu]) = *reinterpret_cast<const u32x4*>(src + (size_t)(r0 + y) * C + c0 + cu);
+    __syncthreads();
+    const int cl = threadIdx.x, c = c0 + cl;   // a column of W, the four quarters of the step
+    if (c >= C) return;
+    const size_t frag = (size_t)(c >> 4) * (R >> 5) + (r0 >> 5);
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+        unsigned w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            w[e] = (unsigned)tile[gq * 8 + 2 * e][cl] | ((unsigned)tile[gq * 8 + 2 * e + 1][cl] << 16);
+        *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(dst) + frag * PF_FRAG_BYTES + gq * 256 + (c & 15) * 16) =
+            u32x4{w[0], w[1], w[2], w[3]};
     }
 }
 
@@ -302,12 +340,27 @@ __global__ __launch_bounds__(256) void k_fit_transpose(const bf16_t* __restrict_
 // and holds D[rows 4 (l / 16) .. + 3][col l % 16]; a lane loads four consecutive k of its row at once, and which four k a
 // lane group takes does not matter as long as both operands take the same.  G is symmetric: only the 128 x 128 blocks on
 // and above the diagonal are computed (the others stay zero) and k_fit_dot counts a block above the diagonal twice. ----
-__global__ __launch_bounds__(256) void k_fit_gram(const float* __restrict__ A, int T, int w, int k_per_wg, float* __restrict__ G) {
-    if (blockIdx.y < blockIdx.x) return;   // below the diagonal
+struct FitGramPart { const float* A; int w; };
+struct FitGram {
+    FitGramPart part[3];   // matrices [T][w] whose Gram matrices are added
+    int slice0[4];         // first slice of each (blockIdx.y)
+    int n, k_per, T;       // columns per slice
+    float* G;
+};
+__global__ __launch_bounds__(256) void k_fit_gram(FitGram p) {
+    // block (bi, bj), bi <= bj, of the upper triangle: blockIdx.x counts it column by column
+    int bj = 0;
+    while ((bj + 1) * (bj + 2) / 2 <= (int)blockIdx.x) ++bj;
+    const int bi = (int)blockIdx.x - bj * (bj + 1) / 2;
+    int m = 0;
+    while (m + 1 < p.n && (int)blockIdx.y >= p.slice0[m + 1]) ++m;
+    const float* __restrict__ A = p.part[m].A;
+    float* __restrict__ G = p.G;
+    const int w = p.part[m].w, T = p.T;
     // a workgroup owns a 128 x 128 block of G, wave (wr, wc) its 64 x 64 quarter: 4 + 4 operand loads feed 64 instructions
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, gq = lane >> 4;
-    const int i0 = blockIdx.x * 128 + (wave >> 1) * 64, j0 = blockIdx.y * 128 + (wave & 1) * 64;
-    const int k_lo = blockIdx.z * k_per_wg, k_hi = min(w, k_lo + k_per_wg);
+    const int i0 = bi * 128 + (wave >> 1) * 64, j0 = bj * 128 + (wave & 1) * 64;
+    const int k_lo = ((int)blockIdx.y - p.slice0[m]) * p.k_per, k_hi = min(w, k_lo + p.k_per);
     const float *ar[4], *br[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -319,12 +372,21 @@ __global__ __launch_bounds__(256) void k_fit_gram(const float* __restrict__ A, i
     for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // operands one step ahead of the instructions that use them (the last step loads itself again, unused)
+    f32x4 an[4], bn[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        an[c] = *reinterpret_cast<const f32x4*>(ar[c] + k_lo);
+        bn[c] = *reinterpret_cast<const f32x4*>(br[c] + k_lo);
+    }
     for (int k0 = k_lo; k0 < k_hi; k0 += 16) {
         f32x4 a[4], b[4];
+        const int k1 = min(k0 + 16, k_hi - 16);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            a[c] = *reinterpret_cast<const f32x4*>(ar[c] + k0);
-            b[c] = *reinterpret_cast<const f32x4*>(br[c] + k0);
+            a[c] = an[c]; b[c] = bn[c];
+            an[c] = *reinterpret_cast<const f32x4*>(ar[c] + k1);
+            bn[c] = *reinterpret_cast<const f32x4*>(br[c] + k1);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)

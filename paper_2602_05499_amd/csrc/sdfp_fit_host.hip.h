@@ -92,7 +92,7 @@ size_t fit_tcache_offset(const FitDims& D, int l, int slot) {
 }
 size_t fit_tcache_bytes(const FitDims& D) { return fit_tcache_offset(D, D.L, 0) + up256((size_t)D.V * D.d * 2); }
 
-// out (+)= X W^T: X [T][K] float32, W [N][K] bfloat16 row-major, out [T][ldo]
+// out = base + X W^T (base may be out, or nullptr for zero): X [T][K] float32, W [N][K] bfloat16, out and base [T][ldo]
 template <int NT, bool PARTIAL>
 void fit_gemm_launch(const Fit& F, const PfGemm& a) {
     static bool attr_done = false;   // per kernel instance
@@ -106,17 +106,19 @@ void fit_gemm_launch(const Fit& F, const PfGemm& a) {
 }
 // A weight operand: the matrix and whether it lies in tile order (pf_tile_weights) or row-major
 struct FitW { const void* p; bool tiled; };
-void fit_gemm(const Fit& F, FitW Wt, int N, int K, const float* X, float* out, int ldo, bool accumulate) {
+// split_done: X is what the previous call multiplied, its pieces are in place
+void fit_gemm(const Fit& F, FitW Wt, int N, int K, const float* X, const float* base, float* out, int ldo, bool split_done = false) {
     const void* W = Wt.p;
     const int T = F.D.T;
     bf16_t* xs = reinterpret_cast<bf16_t*>(F.ws + F.cv.xs);
-    hipLaunchKernelGGL(k_pf_split, dim3(1024), dim3(256), 0, F.st, X, (const float*)nullptr, T, K, xs, pf_xs_piece(T, K));
+    if (!split_done)
+        hipLaunchKernelGGL(k_pf_split, dim3(1024), dim3(256), 0, F.st, X, (const float*)nullptr, T, K, xs, pf_xs_piece(T, K));
     PfGemm a;
     std::memset(&a, 0, sizeof(a));
     a.w[0] = reinterpret_cast<const bf16_t*>(W);
     a.wt = Wt.tiled ? a.w[0] : nullptr;
     a.xs = xs; a.xs_piece = pf_xs_piece(T, K); a.Kd = K; a.n_tiles = N / 16; a.M = T;
-    a.out = out; a.ldo = ldo; a.accumulate = accumulate ? 1 : 0;
+    a.out = out; a.ldo = ldo; a.base = base;
     a.my = (T + PF_TM - 1) / PF_TM; a.n_groups = 1;
     const int fill = (F.n_cu * 3) / 8;
     if (((a.n_tiles + 23) / 24) * a.my >= fill) {
@@ -124,13 +126,12 @@ void fit_gemm(const Fit& F, FitW Wt, int N, int K, const float* X, float* out, i
         fit_gemm_launch<3, false>(F, a);
     } else if (N <= std::max(F.D.d, F.D.hq) && ((a.n_tiles + 31) / 32) * a.my * PF_NSHARE >= fill) {
         // few outputs but many rows: large tiles, a tile's shares dealt to several workgroups (as the prompt path does
-        // for its O and down projections), the shares' sums added in order by k_pf_residual
+        // for its O and down projections), the shares' sums added in order by k_pf_residual (ldo is N there)
         a.n_nt = (a.n_tiles + 31) / 32;
         while (a.n_groups < PF_NSHARE && a.n_nt * a.my * a.n_groups < (F.n_cu * 3) / 4) a.n_groups *= 2;
         a.part = F.f(F.cv.shares); a.part_arr = (size_t)T * N; a.part_ld = N;
         fit_gemm_launch<4, true>(F, a);
-        if (!accumulate) (void)hipMemsetAsync(out, 0, (size_t)T * N * 4, F.st);
-        hipLaunchKernelGGL(k_pf_residual, dim3(512), dim3(256), 0, F.st, out, F.f(F.cv.shares), a.part_arr, T * N / 4);
+        hipLaunchKernelGGL(k_pf_residual, dim3(512), dim3(256), 0, F.st, base, out, F.f(F.cv.shares), a.part_arr, T * N / 4);
     } else {
         a.n_nt = (a.n_tiles + 7) / 8;
         fit_gemm_launch<1, false>(F, a);
@@ -140,7 +141,7 @@ void fit_gemm(const Fit& F, FitW Wt, int N, int K, const float* X, float* out, i
 FitW fit_transposed(const Fit& F, const void* W, int R, int C, int l, int slot) {
     bf16_t* dst = reinterpret_cast<bf16_t*>(F.tcache ? F.tcache + fit_tcache_offset(F.D, l, slot) : F.ws + F.cv.wT);
     if (!F.tcache || F.tfill)
-        hipLaunchKernelGGL(k_fit_transpose, dim3((C + 31) / 32, (R + 31) / 32), dim3(256), 0, F.st,
+        hipLaunchKernelGGL(k_fit_transpose, dim3((C + FIT_TR_COLS - 1) / FIT_TR_COLS, (R + 31) / 32), dim3(256), 0, F.st,
                            reinterpret_cast<const bf16_t*>(W), R, C, dst);
     return FitW{dst, true};
 }
@@ -156,18 +157,38 @@ FitW fit_forward(const Fit& F, const void* W, int N, int K, int l, int slot) {
     }
     return FitW{dst, true};
 }
-void fit_gram(const Fit& F, const float* A, int w, float* G) {
-    const int T = F.D.T, tb = (T + 127) / 128;
+// G = sum of the Gram matrices of up to three matrices
+void fit_gram(const Fit& F, std::initializer_list<FitGramPart> parts, float* G) {
+    const int T = F.D.T, tb = (T + 127) / 128, blocks = tb * (tb + 1) / 2;
     (void)hipMemsetAsync(G, 0, (size_t)T * T * 4, F.st);
-    int ks = std::max(1, std::min(FIT_GRAM_SLICES, w / 128));
-    const int k_per = ((w + ks - 1) / ks + 15) / 16 * 16;
-    ks = (w + k_per - 1) / k_per;
-    hipLaunchKernelGGL(k_fit_gram, dim3(tb, tb, ks), dim3(256), 0, F.st, A, T, w, k_per, G);
+    FitGram p;
+    std::memset(&p, 0, sizeof(p));
+    p.T = T; p.G = G;
+    int w_all = 0;
+    for (const FitGramPart& a : parts) w_all += a.w;
+    // slices: at most FIT_GRAM_SLICES and 128 columns long at least, and of those the largest number whose workgroups make
+    // whole rounds of the compute units (512 positions: 25 slices x 10 blocks, one round, where 32 slices were 1.25)
+    int ks = std::max(1, std::min(FIT_GRAM_SLICES, w_all / 128));
+    const int rounds = ks * blocks / F.n_cu;
+    if (rounds > 0) ks = rounds * F.n_cu / blocks;
+    p.k_per = ((w_all + ks - 1) / ks + 15) / 16 * 16;
+    for (;; p.k_per += 16) {   // (a matrix's last slice may be short: longer slices until their number fits)
+        int slices = 0;
+        for (const FitGramPart& a : parts) slices += (a.w + p.k_per - 1) / p.k_per;
+        if (slices <= std::max(ks, (int)parts.size())) break;
+    }
+    for (const FitGramPart& a : parts) {
+        p.part[p.n] = a;
+        p.slice0[p.n + 1] = p.slice0[p.n] + (a.w + p.k_per - 1) / p.k_per;
+        ++p.n;
+    }
+    hipLaunchKernelGGL(k_fit_gram, dim3(blocks, p.slice0[p.n]), dim3(256), 0, F.st, p);
 }
-// *acc += || dY^T X ||_F^2 with the Gram matrix of X already in GX
-void fit_weight_norm(const Fit& F, const float* dY, int w_out, double* acc) {
+// *acc += sum || dY^T X ||_F^2 over the gradients dY of the matrices that share the input X, whose Gram matrix is in GX:
+// the sum over the product with GX is linear, so their Gram matrices are added first
+void fit_weight_norm(const Fit& F, std::initializer_list<FitGramPart> dYs, double* acc) {
     float* GD = F.f(F.cv.GD);
-    fit_gram(F, dY, w_out, GD);
+    fit_gram(F, dYs, GD);
     hipLaunchKernelGGL(k_fit_dot, dim3(256), dim3(256), 0, F.st, F.f(F.cv.GX), GD, F.D.T, acc);
 }
 
@@ -245,34 +266,32 @@ void fit_sample(const Fit& F, const sd_config* cfg, const sd_weights* w) {
         float *gt = F.f(cv.gt) + l * TF, *up = F.f(cv.up) + l * TF;
         hipLaunchKernelGGL(k_fit_rmsnorm, dim3(T), dim3(256), 0, F.st, x1, (const float*)w->attn_norm[l], D.d, cfg->rms_eps, n,
                            F.f(cv.rs1) + (size_t)l * T);
-        fit_gemm(F, fit_forward(F, w->wq[l], D.hq, D.d, l, 0), D.hq, D.d, n, qr, D.hq, false);
-        fit_gemm(F, fit_forward(F, w->wk[l], D.hkv, D.d, l, 1), D.hkv, D.d, n, kr, D.hkv, false);
-        fit_gemm(F, fit_forward(F, w->wv[l], D.hkv, D.d, l, 2), D.hkv, D.d, n, v, D.hkv, false);
+        fit_gemm(F, fit_forward(F, w->wq[l], D.hq, D.d, l, 0), D.hq, D.d, n, nullptr, qr, D.hq);
+        fit_gemm(F, fit_forward(F, w->wk[l], D.hkv, D.d, l, 1), D.hkv, D.d, n, nullptr, kr, D.hkv, true);
+        fit_gemm(F, fit_forward(F, w->wv[l], D.hkv, D.d, l, 2), D.hkv, D.d, n, nullptr, v, D.hkv, true);
         hipLaunchKernelGGL(k_fit_rope, dim3(T), dim3(256), 0, F.st, qr, D.H, D.hd, cosT, sinT, 0);
         hipLaunchKernelGGL(k_fit_rope, dim3(T), dim3(256), 0, F.st, kr, D.Hkv, D.hd, cosT, sinT, 0);
         fit_attention_fwd(F, qr, kr, v, F.f(cv.P) + l * PP, att);
-        (void)hipMemcpyAsync(x2, x1, Td * 4, hipMemcpyDeviceToDevice, F.st);
-        fit_gemm(F, fit_forward(F, w->wo[l], D.d, D.hq, l, 3), D.d, D.hq, att, x2, D.d, true);
+        fit_gemm(F, fit_forward(F, w->wo[l], D.d, D.hq, l, 3), D.d, D.hq, att, x1, x2, D.d);
         hipLaunchKernelGGL(k_fit_rmsnorm, dim3(T), dim3(256), 0, F.st, x2, (const float*)w->ffn_norm[l], D.d, cfg->rms_eps, n,
                            F.f(cv.rs2) + (size_t)l * T);
-        fit_gemm(F, fit_forward(F, w->w_gate[l], D.F, D.d, l, 4), D.F, D.d, n, gt, D.F, false);
-        fit_gemm(F, fit_forward(F, w->w_up[l], D.F, D.d, l, 5), D.F, D.d, n, up, D.F, false);
+        fit_gemm(F, fit_forward(F, w->w_gate[l], D.F, D.d, l, 4), D.F, D.d, n, nullptr, gt, D.F);
+        fit_gemm(F, fit_forward(F, w->w_up[l], D.F, D.d, l, 5), D.F, D.d, n, nullptr, up, D.F, true);
         hipLaunchKernelGGL(k_fit_swiglu, ew_grid(TF), dim3(256), 0, F.st, gt, up, TF, act);
-        (void)hipMemcpyAsync(x1n, x2, Td * 4, hipMemcpyDeviceToDevice, F.st);
-        fit_gemm(F, fit_forward(F, w->w_down[l], D.d, D.F, l, 6), D.d, D.F, act, x1n, D.d, true);
+        fit_gemm(F, fit_forward(F, w->w_down[l], D.d, D.F, l, 6), D.d, D.F, act, x2, x1n, D.d);
     }
     float* hL = F.f(cv.x1) + (size_t)L * Td;
     float* logits = F.f(cv.logits);
     hipLaunchKernelGGL(k_fit_rmsnorm, dim3(T), dim3(256), 0, F.st, hL, (const float*)w->final_norm, D.d, cfg->rms_eps, n,
                        F.f(cv.rsf));
-    fit_gemm(F, fit_forward(F, w->lm_head, D.V, D.d, L, 0), D.V, D.d, n, logits, D.V, false);
+    fit_gemm(F, fit_forward(F, w->lm_head, D.V, D.d, L, 0), D.V, D.d, n, nullptr, logits, D.V);
     (void)hipMemsetAsync(scores + 2 * L, 0, sizeof(double), F.st);
     hipLaunchKernelGGL(k_fit_ce, dim3(T), dim3(256), 0, F.st, logits, tokens, T, D.V, scores + 2 * L);
 
     // ---- backward.  dh: gradient of the residual stream entering the part of the network still to be walked.
     float *dh = F.f(cv.dh), *dn = F.f(cv.dn), *dq = F.f(cv.dq), *dk = F.f(cv.dk), *dv = F.f(cv.dv), *datt = F.f(cv.datt);
     float *dact = F.f(cv.dact), *dgt = F.f(cv.dgt), *dup = F.f(cv.dup), *dS = F.f(cv.dS), *GX = F.f(cv.GX);
-    fit_gemm(F, fit_transposed(F, w->lm_head, D.V, D.d, L, 0), D.d, D.V, logits, dn, D.d, false);
+    fit_gemm(F, fit_transposed(F, w->lm_head, D.V, D.d, L, 0), D.d, D.V, logits, nullptr, dn, D.d);
     hipLaunchKernelGGL(k_fit_rmsnorm_bwd, dim3(T), dim3(256), 0, F.st, hL, (const float*)w->final_norm, F.f(cv.rsf), dn, D.d,
                        (const float*)nullptr, dh);
     for (int l = L - 1; l >= 0; --l) {
@@ -283,35 +302,32 @@ void fit_sample(const Fit& F, const sd_config* cfg, const sd_weights* w) {
         double *s_attn = scores + l, *s_ffn = scores + L + l;
         // feed-forward sub-layer: h_out = x2 + act W_down^T
         hipLaunchKernelGGL(k_fit_swiglu, ew_grid(TF), dim3(256), 0, F.st, gt, up, TF, act);
-        fit_gram(F, act, D.F, GX);
-        fit_weight_norm(F, dh, D.d, s_ffn);                                              // w_down
-        fit_gemm(F, fit_transposed(F, w->w_down[l], D.d, D.F, l, 6), D.F, D.d, dh, dact, D.F, false);
+        fit_gram(F, {{act, D.F}}, GX);
+        fit_weight_norm(F, {{dh, D.d}}, s_ffn);                                              // w_down
+        fit_gemm(F, fit_transposed(F, w->w_down[l], D.d, D.F, l, 6), D.F, D.d, dh, nullptr, dact, D.F);
         hipLaunchKernelGGL(k_fit_swiglu_bwd, ew_grid(TF), dim3(256), 0, F.st, dact, gt, up, TF, dgt, dup);
         hipLaunchKernelGGL(k_fit_rmsnorm, dim3(T), dim3(256), 0, F.st, x2, (const float*)w->ffn_norm[l], D.d, cfg->rms_eps, n, dn);
         // (the reciprocal RMS written to dn above is scratch: rs2 is the kept one)
-        fit_gram(F, n, D.d, GX);
-        fit_weight_norm(F, dgt, D.F, s_ffn);                                             // w_gate
-        fit_weight_norm(F, dup, D.F, s_ffn);                                             // w_up
-        fit_gemm(F, fit_transposed(F, w->w_gate[l], D.F, D.d, l, 4), D.d, D.F, dgt, dn, D.d, false);
-        fit_gemm(F, fit_transposed(F, w->w_up[l], D.F, D.d, l, 5), D.d, D.F, dup, dn, D.d, true);
+        fit_gram(F, {{n, D.d}}, GX);
+        fit_weight_norm(F, {{dgt, D.F}, {dup, D.F}}, s_ffn);                             // w_gate, w_up
+        fit_gemm(F, fit_transposed(F, w->w_gate[l], D.F, D.d, l, 4), D.d, D.F, dgt, nullptr, dn, D.d);
+        fit_gemm(F, fit_transposed(F, w->w_up[l], D.F, D.d, l, 5), D.d, D.F, dup, dn, dn, D.d);
         hipLaunchKernelGGL(k_fit_dgain_sumsq, dim3((D.d + 63) / 64), dim3(1024), 0, F.st, x2, rs2, dn, T, D.d, s_ffn);   // ffn_norm
         hipLaunchKernelGGL(k_fit_rmsnorm_bwd, dim3(T), dim3(256), 0, F.st, x2, (const float*)w->ffn_norm[l], rs2, dn, D.d,
                            (const float*)dh, dh);                                        // dh = gradient at x2
         // attention sub-layer: x2 = x1 + att W_o^T
-        fit_gram(F, att, D.hq, GX);
-        fit_weight_norm(F, dh, D.d, s_attn);                                             // wo
-        fit_gemm(F, fit_transposed(F, w->wo[l], D.d, D.hq, l, 3), D.hq, D.d, dh, datt, D.hq, false);
+        fit_gram(F, {{att, D.hq}}, GX);
+        fit_weight_norm(F, {{dh, D.d}}, s_attn);                                             // wo
+        fit_gemm(F, fit_transposed(F, w->wo[l], D.d, D.hq, l, 3), D.hq, D.d, dh, nullptr, datt, D.hq);
         fit_attention_bwd(F, datt, qr, kr, v, P, dS, dq, dk, dv);
         hipLaunchKernelGGL(k_fit_rope, dim3(T), dim3(256), 0, F.st, dq, D.H, D.hd, cosT, sinT, 1);
         hipLaunchKernelGGL(k_fit_rope, dim3(T), dim3(256), 0, F.st, dk, D.Hkv, D.hd, cosT, sinT, 1);
         hipLaunchKernelGGL(k_fit_rmsnorm, dim3(T), dim3(256), 0, F.st, x1, (const float*)w->attn_norm[l], D.d, cfg->rms_eps, n, dn);
-        fit_gram(F, n, D.d, GX);
-        fit_weight_norm(F, dq, D.hq, s_attn);                                            // wq
-        fit_weight_norm(F, dk, D.hkv, s_attn);                                           // wk
-        fit_weight_norm(F, dv, D.hkv, s_attn);                                           // wv
-        fit_gemm(F, fit_transposed(F, w->wq[l], D.hq, D.d, l, 0), D.d, D.hq, dq, dn, D.d, false);
-        fit_gemm(F, fit_transposed(F, w->wk[l], D.hkv, D.d, l, 1), D.d, D.hkv, dk, dn, D.d, true);
-        fit_gemm(F, fit_transposed(F, w->wv[l], D.hkv, D.d, l, 2), D.d, D.hkv, dv, dn, D.d, true);
+        fit_gram(F, {{n, D.d}}, GX);
+        fit_weight_norm(F, {{dq, D.hq}, {dk, D.hkv}, {dv, D.hkv}}, s_attn);              // wq, wk, wv
+        fit_gemm(F, fit_transposed(F, w->wq[l], D.hq, D.d, l, 0), D.d, D.hq, dq, nullptr, dn, D.d);
+        fit_gemm(F, fit_transposed(F, w->wk[l], D.hkv, D.d, l, 1), D.d, D.hkv, dk, dn, dn, D.d);
+        fit_gemm(F, fit_transposed(F, w->wv[l], D.hkv, D.d, l, 2), D.d, D.hkv, dv, dn, dn, D.d);
         hipLaunchKernelGGL(k_fit_dgain_sumsq, dim3((D.d + 63) / 64), dim3(1024), 0, F.st, x1, rs1, dn, T, D.d, s_attn);  // attn_norm
         hipLaunchKernelGGL(k_fit_rmsnorm_bwd, dim3(T), dim3(256), 0, F.st, x1, (const float*)w->attn_norm[l], rs1, dn, D.d,
                            (const float*)dh, dh);                                        // dh = gradient at x1

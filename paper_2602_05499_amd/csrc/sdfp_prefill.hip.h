@@ -48,7 +48,7 @@ __host__ __device__ __forceinline__ size_t pf_xs_off(int m, int k8, int Kd) {
 }
 __host__ __device__ __forceinline__ size_t pf_xs_piece(int rows, int Kd) { return (size_t)((rows + 15) / 16 * 16) * (size_t)Kd; }
 
-enum { PF_QKV = 0, PF_OPROJ = 1, PF_GATEUP = 2, PF_DOWN = 3, PF_PLAIN = 4 };   // PF_PLAIN: out = (out +) x W^T, nothing fused
+enum { PF_QKV = 0, PF_OPROJ = 1, PF_GATEUP = 2, PF_DOWN = 3, PF_PLAIN = 4 };   // PF_PLAIN: out = (base +) x W^T, nothing fused
 
 struct PfGemm {
     const bf16_t* w[3];      // QKV: wq wk wv; gate/up: w_gate w_up; else the matrix in w[0]; row-major [N][Kd]
@@ -68,7 +68,7 @@ struct PfGemm {
     const float *cosT, *sinT;
     float* out;              // PF_PLAIN: [M][ldo] float32 result
     int ldo;                 // PF_PLAIN: elements between rows of out
-    int accumulate;          // PF_PLAIN: add to what out holds instead of overwriting it
+    const float* base;       // PF_PLAIN: [M][ldo] float32 added to the product (may be out), or nullptr
     float* part;             // a projection dealt by shares: [8][P][part_ld] partial sums
     size_t part_arr;         // floats per array of part (P * part_ld)
     int part_ld;             // floats per row of part: the projection's outputs (16 * n_tiles)
@@ -440,8 +440,8 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
             if (KIND == PF_PLAIN) {
                 if (m < a.M) {
                     float* o = a.out + (size_t)m * a.ldo + tile * 16 + gq * 4;
-                    if (a.accumulate) {
-                        const f32x4 r = *reinterpret_cast<const f32x4*>(o);
+                    if (a.base != nullptr) {
+                        const f32x4 r = *reinterpret_cast<const f32x4*>(a.base + (size_t)m * a.ldo + tile * 16 + gq * 4);
                         v = f32x4{add_rn(r.x, v.x), add_rn(r.y, v.y), add_rn(r.z, v.z), add_rn(r.w, v.w)};
                     }
                     *reinterpret_cast<f32x4*>(o) = v;
@@ -504,8 +504,9 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
 }
 
 
-// O / down projection in PARTIAL form: h[m][n] += ((((0 + P0) + P1) + ...) + P7), 4 outputs per thread
-__global__ __launch_bounds__(256) void k_pf_residual(float* __restrict__ h, const float* __restrict__ part, size_t part_arr, int n4) {
+// O / down projection in PARTIAL form: h = base + ((((0 + P0) + P1) + ...) + P7), 4 outputs per thread; base may be h, or
+// nullptr for zero
+__global__ __launch_bounds__(256) void k_pf_residual(const float* base, float* h, const float* __restrict__ part, size_t part_arr, int n4) {
     for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n4; c += gridDim.x * blockDim.x) {
         f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -513,7 +514,7 @@ __global__ __launch_bounds__(256) void k_pf_residual(float* __restrict__ h, cons
             const f32x4 v = *reinterpret_cast<const f32x4*>(part + (size_t)p * part_arr + (size_t)c * 4);
             t = f32x4{add_rn(t.x, v.x), add_rn(t.y, v.y), add_rn(t.z, v.z), add_rn(t.w, v.w)};
         }
-        const f32x4 r = *reinterpret_cast<const f32x4*>(h + (size_t)c * 4);
+        const f32x4 r = base != nullptr ? *reinterpret_cast<const f32x4*>(base + (size_t)c * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
         *reinterpret_cast<f32x4*>(h + (size_t)c * 4) = f32x4{add_rn(r.x, t.x), add_rn(r.y, t.y), add_rn(r.z, t.z), add_rn(r.w, t.w)};
     }
 }

@@ -88,6 +88,14 @@ def test_fit_scores_long_sequence(gpu, small_shapes):
     _compare(gpu, s, 600, 1)
 
 
+@pytest.mark.parametrize("T", [2, 15, 16, 17, 66, 129, 260])
+def test_fit_scores_ragged_sequence_lengths(gpu, small_shapes, T):
+    """Attention products whose summed index is the sequence: no whole step of 16, whole steps with and without a ragged
+    end, rows that do and do not allow 16-byte loads (T a multiple of 4 or not); one, two and three Gram blocks a side."""
+    s = small_shapes["gqa_bf16"].with_(name="fit_gqa_T", vocab=96, init_std=0.15)
+    _compare(gpu, s, T, 1)
+
+
 def test_fit_scores_head_dim_64_and_several_panels_of_keys(gpu):
     """head_dim 64, d 256, a 130-token sequence (three 64-row tiles, attention rows longer than a wave)."""
     s = synth.CONFIGS["tiny"].with_(name="fit_hd64", dtype="bf16", d_ffn=704, vocab=512, gain_std=0.1, init_std=0.05)
