@@ -136,15 +136,18 @@ __device__ __forceinline__ int chunked_inv_cdf(double cw, int V, int len, double
     return s_tok;
 }
 
-// maximum and sum of exp((z - maximum) / T) of chunk c of a row
+// maximum and sum of exp((z - maximum) / T) of chunk c of a row.  A chunk whose entries are all -inf (masked or overflowed
+// logits) has the sum 0: exp(-inf - -inf) would be NaN and take the whole row with it.  (Its maximum stays -inf, which
+// gives it the weight exp(-inf) = 0 where the chunks are combined; a row that is -inf throughout stays NaN there.)
 __device__ __forceinline__ void chunk_stats(const float* __restrict__ z, int V, int len, int c, double invT, double* sh, float* mx_out,
                                             double* sum_out) {
     const int lo = c * len, hi = min(V, lo + len);
     float mx = -INFINITY;
     for (int j = lo + threadIdx.x; j < hi; j += SEL_THREADS) mx = fmaxf(mx, z[j]);
     mx = block_max_f(mx, sh);
+    const double ref = mx > -INFINITY ? (double)mx : 0.0;
     double s = 0.0;
-    for (int j = lo + threadIdx.x; j < hi; j += SEL_THREADS) s += exp(((double)z[j] - (double)mx) * invT);
+    for (int j = lo + threadIdx.x; j < hi; j += SEL_THREADS) s += exp(((double)z[j] - ref) * invT);
     *sum_out = block_sum_d(s, sh);
     *mx_out = mx;
 }
