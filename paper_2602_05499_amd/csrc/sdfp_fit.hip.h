@@ -11,12 +11,12 @@
 // accumulation); Gram matrices through the float32 matrix-core instruction; attention, norms, rotary embedding, SwiGLU
 // and the cross-entropy on the vector ALUs.  Keys and values are not rounded: there is no cache in this pass.
 #pragma once
+#include "sdfp_fit_plan.h"
 #include "sdfp_prefill.hip.h"
 
 namespace sdfp {
 
 constexpr int FIT_MAX_T = 2048;   // positions per calibration sequence (an attention row of probabilities is kept in LDS)
-constexpr int FIT_GRAM_SLICES = 32;   // most stretches the reduction dimension of a Gram matrix is cut into
 
 __device__ __forceinline__ float fit_wave_sum(float v) {
 #pragma unroll
@@ -342,9 +342,9 @@ __global__ __launch_bounds__(256) void k_fit_transpose(const bf16_t* __restrict_
 // and above the diagonal are computed (the others stay zero) and k_fit_dot counts a block above the diagonal twice. ----
 struct FitGramPart { const float* A; int w; };
 struct FitGram {
-    FitGramPart part[3];   // matrices [T][w] whose Gram matrices are added
-    int slice0[4];         // first slice of each (blockIdx.y)
-    int n, k_per, T;       // columns per slice
+    FitGramPart part[FIT_GRAM_PARTS];   // matrices [T][w] whose Gram matrices are added
+    int slice0[FIT_GRAM_PARTS + 1];     // first slice of each (blockIdx.y)
+    int n, k_per, T;                    // columns per slice
     float* G;
 };
 __global__ __launch_bounds__(256) void k_fit_gram(FitGram p) {

@@ -164,24 +164,11 @@ void fit_gram(const Fit& F, std::initializer_list<FitGramPart> parts, float* G) 
     FitGram p;
     std::memset(&p, 0, sizeof(p));
     p.T = T; p.G = G;
-    int w_all = 0;
-    for (const FitGramPart& a : parts) w_all += a.w;
-    // slices: at most FIT_GRAM_SLICES and 128 columns long at least, and of those the largest number whose workgroups make
-    // whole rounds of the compute units (512 positions: 25 slices x 10 blocks, one round, where 32 slices were 1.25)
-    int ks = std::max(1, std::min(FIT_GRAM_SLICES, w_all / 128));
-    const int rounds = ks * blocks / F.n_cu;
-    if (rounds > 0) ks = rounds * F.n_cu / blocks;
-    p.k_per = ((w_all + ks - 1) / ks + 15) / 16 * 16;
-    for (;; p.k_per += 16) {   // (a matrix's last slice may be short: longer slices until their number fits)
-        int slices = 0;
-        for (const FitGramPart& a : parts) slices += (a.w + p.k_per - 1) / p.k_per;
-        if (slices <= std::max(ks, (int)parts.size())) break;
-    }
-    for (const FitGramPart& a : parts) {
-        p.part[p.n] = a;
-        p.slice0[p.n + 1] = p.slice0[p.n] + (a.w + p.k_per - 1) / p.k_per;
-        ++p.n;
-    }
+    int w[FIT_GRAM_PARTS];
+    for (const FitGramPart& a : parts) { w[p.n] = a.w; p.part[p.n++] = a; }
+    const FitGramSlices sl = fit_gram_slices(T, w, p.n, F.n_cu);
+    p.k_per = sl.k_per;
+    std::memcpy(p.slice0, sl.slice0, sizeof(p.slice0));
     hipLaunchKernelGGL(k_fit_gram, dim3(blocks, p.slice0[p.n]), dim3(256), 0, F.st, p);
 }
 // *acc += sum || dY^T X ||_F^2 over the gradients dY of the matrices that share the input X, whose Gram matrix is in GX:
