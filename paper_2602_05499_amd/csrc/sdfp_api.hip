@@ -43,7 +43,7 @@ enum StepState { PH_INIT = 0, PH_READY, PH_DRAFTED, PH_VERIFIED, PH_ACCEPTED };
 
 struct Carve {   // byte offsets inside the workspace
     size_t state, out_tokens, prompt, cosT, sinT, acts, part_o, part_ml, counters, zq, zp, head_val, head_idx,
-        prog_target, prog_draft, prog_head, bar, sel, trace, guard_rec, total;
+        prog_target, prog_draft, prog_head, bar, trace, guard_rec, total;
     size_t act_h, act_q, act_a;   // bytes of one residual / query / feed-forward activation block
     size_t acts_bytes;            // bytes of the activation region (also the scratch of the matrix-matrix prompt path)
 };
@@ -182,16 +182,15 @@ Carve carve(const sd_config* c, bool compact = false) {
     k.acts = take(k.acts_bytes);
     k.part_o = take(sizeof(float) * (size_t)n_splits(c) * MAX_ROWS * dq);
     k.part_ml = take(sizeof(float) * (size_t)n_splits(c) * MAX_ROWS * c->n_heads * 2);
-    k.counters = take(sizeof(unsigned) * ((size_t)c->n_kv_heads + 1));   // split merges, and the selection kernels' arrivals
+    k.counters = take(sizeof(unsigned) * (size_t)c->n_kv_heads);
     k.zq = take(sizeof(float) * (size_t)(c->max_k > 0 ? c->max_k : 1) * c->vocab);
     k.zp = take(sizeof(float) * (size_t)(c->max_k + 1) * c->vocab);
-    k.head_val = take(sizeof(float) * HEAD_GRID_MAX * MAX_ROWS);
+    k.head_val = take(sizeof(float) * HEAD_GRID_MAX * MAX_ROWS);   // (the selection kernels' buffers too, see sd_ctx::sel)
     k.head_idx = take(sizeof(int) * HEAD_GRID_MAX * MAX_ROWS);
     k.prog_target = take(sizeof(Phase) * prog_len(c));
     k.prog_draft = take(sizeof(Phase) * prog_len(c));
     k.prog_head = take(sizeof(Phase) * 2);   // the output head alone, for the prompt's last row (matrix-matrix prompt path)
-    k.bar = take(BAR_WORDS * sizeof(unsigned));
-    k.sel = take(sel_buf_bytes());
+    k.bar = take((BAR_WORDS + 1) * sizeof(unsigned));   // and, behind it, the selection kernels' arrival counter
     k.trace = take(sizeof(unsigned long long) * (TRACE_CAP + 1));
     k.guard_rec = take(sizeof(unsigned long long) * 32);
     k.total = off;
@@ -239,13 +238,17 @@ struct sd_ctx {
     int* out_tokens() const { return reinterpret_cast<int*>(ws + cv.out_tokens); }
     int* prompt() const { return reinterpret_cast<int*>(ws + cv.prompt); }
     float* f(size_t off) const { return reinterpret_cast<float*>(ws + off); }
+    // The selection kernels' buffers: the room of the arg-max partials, which a forward writes and reduces within itself,
+    // while these kernels run between two forwards and keep nothing there; the counter lies behind the grid barrier's words
+    // and is cleared with them.  So sampling asks for no workspace of its own.
     SelBuf sel() const {
+        static_assert(sel_buf_bytes() <= sizeof(float) * HEAD_GRID_MAX * MAX_ROWS, "the arg-max partials' room must hold it");
         SelBuf b;
-        b.sum = reinterpret_cast<double*>(ws + cv.sel);
+        b.sum = reinterpret_cast<double*>(ws + cv.head_val);
         b.wres = b.sum + (size_t)SEL_ROWS * SEL_CHUNKS;
         b.wp = b.wres + SEL_CHUNKS;
         b.mx = reinterpret_cast<float*>(b.wp + SEL_CHUNKS);
-        b.counter = reinterpret_cast<unsigned*>(ws + cv.counters) + cfg.n_kv_heads;
+        b.counter = reinterpret_cast<unsigned*>(ws + cv.bar) + BAR_WORDS;
         return b;
     }
 };
@@ -444,8 +447,8 @@ int lazy_device_init(sd_ctx* c) {
     z.max_out = g.max_out;
     HIPCHK(c, hipMemcpyAsync(c->st(), &z, sizeof(z), hipMemcpyHostToDevice, c->stream));
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(256), 0, c->stream,
-                       reinterpret_cast<unsigned*>(c->ws + c->cv.counters), g.n_kv_heads + 1);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.bar), BAR_WORDS);
+                       reinterpret_cast<unsigned*>(c->ws + c->cv.counters), g.n_kv_heads);
+    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.bar), BAR_WORDS + 1);
     // the diagnostics' records start empty whatever the workspace held before
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream,
                        reinterpret_cast<unsigned*>(c->ws + c->cv.trace + sizeof(unsigned long long) * TRACE_CAP), 2);
@@ -821,9 +824,9 @@ int do_prefill(sd_ctx* c, const int32_t* prompt_host, int n, int mode, const flo
     HIPCHK(c, hipMemcpyAsync(c->prompt(), prompt_host, sizeof(int) * (size_t)n, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));   // prompt_host may be reused by the caller on return
     // a fresh sequence starts from clean barrier and split-merge counters (also the way out of SD_ETIMEOUT)
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.bar), BAR_WORDS);
+    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.bar), BAR_WORDS + 1);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.counters),
-                       c->cfg.n_kv_heads + 1);
+                       c->cfg.n_kv_heads);
     const bool keep = mode == SD_SAMPLE || c->keep_logits;
     const bool gemm = std::is_same<WT, bf16_t>::value && c->panel.P > 0 &&
                       (c->prefill_mode == 1 || (c->prefill_mode < 0 && n >= PREFILL_MATRIX_MIN_ROWS));

@@ -90,6 +90,22 @@ def test_size_functions_follow_the_documented_layout(lib):
     assert B.sd_tiled_weights_bytes(_config(B, head_dim=48)) == 0
 
 
+def test_a_static_context_at_the_limit_of_its_array_is_accepted(lib):
+    """The largest committed-token list that the 64 MiB of a static context hold for a small float32 model, one 256-byte
+    step of it more, and the workspace of two plain configurations: sizes that callers' buffers were made for stay enough."""
+    from paper_2602_05499_amd import binding as B
+    limit = 64 << 20
+    assert B.sd_workspace_bytes(_config(B)) == 13286400
+    assert B.sd_workspace_bytes(_config(B, dtype=B.SD_F32, n_heads=64, n_kv_heads=64)) == 2912768
+    for max_out, fits in ((16604160, True), (16604161, False)):
+        cfg, w, arrs, fake = _fake_context(B, dtype=B.SD_F32, max_out=max_out)
+        assert (B.sd_workspace_bytes(cfg) <= limit) == fits
+        rc, ctx = B.sd_init_static(cfg, w, None, fake, B.sd_kv_bytes(cfg), None)
+        assert (rc != B.SD_ENOMEM) == fits      # (without a device the accepted one ends at the look-up of the array)
+        if rc == B.SD_OK:
+            B.sd_free(ctx)
+
+
 @pytest.mark.parametrize("bad", [dict(head_dim=48), dict(head_dim=256), dict(n_heads=3, n_kv_heads=2), dict(max_k=9),
                                  dict(d_model=250), dict(dtype=7), dict(max_seq=3), dict(temperature=0.0),
                                  dict(n_layers=0), dict(vocab=0)])
