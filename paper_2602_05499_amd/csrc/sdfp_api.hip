@@ -2,6 +2,7 @@
 // sequences behind the C-ABI declared in include/sdfp.h (paper Sec. II-A, Alg. 1 Stage B, Sec. III-C).
 #include "sdfp_kernels.hip.h"
 #include "sdfp_prefill.hip.h"
+#include "sdfp_prefill_plan.h"
 #include "sdfp.h"
 
 #include <algorithm>
@@ -596,8 +597,8 @@ int launch_pf_attn(sd_ctx* c, const PfAttn& a, int n_wg) {
     switch (g.head_dim) {
         case 16: SDFP_PF_ATTN(4)
         case 32: SDFP_PF_ATTN(8)
-        case 64: SDFP_PF_ATTN_1(16, false)      // (one split only, see the caller)
-        default: SDFP_PF_ATTN_1(32, false)
+        case 64: SDFP_PF_ATTN(16)
+        default: SDFP_PF_ATTN(32)
     }
 #undef SDFP_PF_ATTN
 #undef SDFP_PF_ATTN_1
@@ -728,26 +729,24 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             t.counters = counters; t.M = np; t.pos0 = p0; t.L = L;
             const int n_chunks = (np + MAX_ROWS - 1) / MAX_ROWS, grp = g.n_heads / g.n_kv_heads;
             const int n_act = (p0 + np + ATT_SL - 1) / ATT_SL;
-            // Attention on the matrix cores wherever it has an instance and work for its waves.  Plain heads within one
-            // split give it a workgroup per head and nothing for half of its waves: k_pf_attn's workgroup per (chunk, head)
-            // is quicker there (7B shape, 37 rows: 24.5 us against 29; from two splits on, or with grouped queries, the
-            // matrix cores win: 512 rows 122 -> 70 us, 77 rows of 16 heads on 4 58 -> 20).
-            if (g.head_dim >= 64 && (n_act > 1 || grp > 1)) {
-                // split partials: the room of the projections' partial sums (idle here) or the regions of k_pf_attn's
-                // workgroups, whichever holds more slots -- never none: 8 regions hold 128 grp >= 64 queries.  With
-                // fewer slots than items a workgroup takes several items.
+            // Attention on the matrix cores (head_dim 64 and 128) or on the vector ALUs: whichever the times of
+            // sdfp_prefill_plan.h say is quicker for this panel.
+            // Split partials of the former: the room of the projections' partial sums (idle here) or the regions of
+            // k_pf_attn's workgroups, whichever holds more slots -- never none: 8 regions hold 128 grp >= 64 queries.  With
+            // fewer slots than items a workgroup takes several items.
+            const size_t slot = pfx_slot_floats(g.head_dim, n_act);
+            const size_t in_shares = (size_t)PF_NSHARE * pl.P * d / slot, in_part = (size_t)pl.n_awg * pl.part_stride / slot;
+            const size_t items = (size_t)((n_chunks * grp + PFX_TILES - 1) / PFX_TILES) * g.n_kv_heads;
+            const int n_wg = (int)std::min(items, std::max(in_shares, in_part));
+            if (g.head_dim >= 64 &&
+                pf_attn_on_matrix_cores(PfAttnPanel{g.head_dim, g.n_kv_heads, grp, np, p0, c->n_cu, pl.n_awg, n_wg})) {
                 PfAttnMx x;
                 std::memset(&x, 0, sizeof(x));
                 x.q = q; x.att = att; x.kc = kc; x.vc = vc; x.M = np; x.pos0 = p0; x.L = L;
-                x.part_stride = pfx_slot_floats(g.head_dim, n_act);
+                x.part_stride = slot;
                 x.part_ml_off = (size_t)n_act * PFX_QUERIES * g.head_dim;
-                const size_t in_shares = (size_t)PF_NSHARE * pl.P * d / x.part_stride;
-                const size_t in_part = (size_t)pl.n_awg * pl.part_stride / x.part_stride;
                 x.part = in_shares >= in_part ? shares : t.part;
-                const size_t items = (size_t)((n_chunks * grp + PFX_TILES - 1) / PFX_TILES) * g.n_kv_heads;
-                const size_t n_wg = std::min(items, std::max(in_shares, in_part));
-                if (n_wg < 1) return SD_EINVAL;
-                if ((e = launch_pf_attn_mx(c, x, (int)n_wg))) return e;
+                if ((e = launch_pf_attn_mx(c, x, n_wg))) return e;
             } else if ((e = launch_pf_attn(c, t, std::min(pl.n_awg, n_chunks * g.n_kv_heads)))) {
                 return e;
             }

@@ -1,0 +1,82 @@
+// Which kernel runs the attention of a prompt panel (host arithmetic only).
+#pragma once
+#include <algorithm>
+
+namespace sdfp {
+
+// One panel: M rows from absolute position pos0, Hkv KV heads of head_dim hd (64 or 128) with grp query heads each.
+struct PfAttnPanel {
+    int hd, Hkv, grp, M, pos0;
+    int n_cu;          // compute units
+    int wg_valu;       // workgroups k_pf_attn may use (regions of split partials)
+    int wg_mx;         // workgroups k_pf_attn_mx may use (slots of split partials)
+};
+constexpr int PF_CHUNK = 16, PF_SPLIT = 128, PF_MX_TILES = 4;   // rows of a chunk, positions of a split, tiles of a k_pf_attn_mx workgroup
+
+inline int pf_chunk_rows(const PfAttnPanel& p, int c) { return std::min(PF_CHUNK, p.M - c * PF_CHUNK); }
+inline int pf_chunk_splits(const PfAttnPanel& p, int c) {
+    return (p.pos0 + c * PF_CHUNK + pf_chunk_rows(p, c) + PF_SPLIT - 1) / PF_SPLIT;
+}
+
+// Both kernels are chains of latencies: a workgroup's time hardly depends on how many others run, and a launch takes as long
+// as its longest workgroup, or the longest sequence of them where they do not all fit at once.  Times in us, fitted to both
+// kernels' times over 1..40 KV heads x 1..8 query heads, 5 to 1568 rows (within 10 % of most; it is the comparison that
+// counts).  Both sides measured, head_dim 128:
+//   4 x 1 heads:  128 rows 24 / 32 (valu / mx), 256 rows 38 / 41, 512 rows 67 / 68, the 512 rows behind 512 124 / 121, one row
+//                 behind 512 23 / 71, 16 rows behind 512 76 / 79, 16 behind 1024 135 / 130
+//   32 x 1 heads: 129 rows 26 / 32, 256 rows 43 / 42, 288 rows 74 / 56, 512 rows 121 / 69
+//   8 x 4 heads:  5 rows 31 / 28, 16 rows 87 / 31, 512 rows 241 / 69, one row behind 512 33 / 76, 8 rows behind 512 148 / 80
+// head_dim 64, 4 x 1 heads: 16 rows 17 / 17, 128 rows 18 / 19, 256 rows 30 / 24, one row behind 1024 31 / 73.
+//
+// k_pf_attn: a workgroup per (16-row chunk, KV head), the chunk's splits one after another, queries in passes of 8; two
+// workgroups share a compute unit (15 % longer).
+inline double pf_valu_item_us(const PfAttnPanel& p, int c) {
+    const int q = pf_chunk_rows(p, c) * p.grp, passes = (q + 7) / 8, n = pf_chunk_splits(p, c);
+    return p.hd == 64 ? 4.0 + 0.19 * q + n * (1.8 + 0.8 * passes + 0.48 * q) : 4.0 + 0.35 * q + n * (2.9 + 0.7 * passes + 0.6 * q);
+}
+inline double pf_valu_us(const PfAttnPanel& p) {
+    const int items = (p.M + PF_CHUNK - 1) / PF_CHUNK * p.Hkv, n_wg = std::min(p.wg_valu, items);
+    double worst = 0.0;
+    // items run in ascending chunk order, a workgroup takes every n_wg-th: the one with the last chunk, and the one with the
+    // chunk before it (the last may have a row or two)
+    for (int first : {items - 1, items - 1 - p.Hkv}) {
+        double t = 0.0;
+        for (int it = first; it >= 0; it -= n_wg) t += pf_valu_item_us(p, it / p.Hkv);
+        worst = std::max(worst, t);
+    }
+    return worst * (n_wg > p.n_cu ? 1.15 : 1.0);
+}
+// k_pf_attn_mx: a workgroup per 4 tiles of a KV head, whose time is that of its longest row, however many query heads the
+// rows have; one workgroup per compute unit, longest first.
+inline double pf_mx_item_us(const PfAttnPanel& p, int tg, int n_tiles) {
+    const int c0 = tg * PF_MX_TILES / p.grp, c1 = (std::min(n_tiles, (tg + 1) * PF_MX_TILES) - 1) / p.grp;
+    const int n = pf_chunk_splits(p, c1), rows = (c1 - c0) * PF_CHUNK + pf_chunk_rows(p, c1);
+    const double fill = std::min(p.grp * rows, 64) / 64.0;   // waves without rows leave more of the unit to the others
+    return p.hd == 64 ? 8.2 + 7.3 * n + 3.0 * fill : 11.5 + 12.7 * n + 7.0 * fill;
+}
+inline double pf_mx_us(const PfAttnPanel& p) {
+    const int n_tiles = (p.M + PF_CHUNK - 1) / PF_CHUNK * p.grp, n_tg = (n_tiles + PF_MX_TILES - 1) / PF_MX_TILES;
+    const int items = n_tg * p.Hkv, n_wg = std::min(p.wg_mx, items);
+    auto item_us = [&](int it) { return pf_mx_item_us(p, n_tg - 1 - it / p.Hkv, n_tiles); };
+    // the workgroup with the last group of tiles, and the one with the group before it (the last may have a row or two)
+    double worst = 0.0;
+    for (int first : {0, p.Hkv}) {
+        double t = 0.0;
+        for (int it = first; it < items; it += n_wg <= p.n_cu ? n_wg : items) t += item_us(it);
+        worst = std::max(worst, t);
+    }
+    if (n_wg > p.n_cu) {   // more than a round: the rest start where the shortest of the first round have ended
+        double all = 0.0;
+        for (int tg = 0; tg < n_tg; ++tg) all += pf_mx_item_us(p, tg, n_tiles);
+        worst = std::max(std::max(worst, item_us(p.n_cu - 1) + item_us(items - 1)), all * p.Hkv / p.n_cu);
+    }
+    return worst;
+}
+// Beyond this many splits the other kernel's merge has no room in LDS for a query's statistics (head_dim 64: 2560).
+constexpr int PF_VALU_MAX_SPLITS = 2048;
+inline bool pf_attn_on_matrix_cores(const PfAttnPanel& p) {
+    if (p.wg_mx < 1) return false;
+    return pf_chunk_splits(p, (p.M - 1) / PF_CHUNK) > PF_VALU_MAX_SPLITS || pf_mx_us(p) <= pf_valu_us(p);
+}
+
+}  // namespace sdfp

@@ -172,6 +172,9 @@ def test_matrix_prompt_path_panel_boundaries(gpu, small_shapes):
     (4, 4, 64, [127, 128, 129, 130, 256, 257]),     # plain heads: vector-ALU kernel within one split, matrix cores beyond
     (8, 1, 128, [16, 17, 129, 1024, 1025]),         # more query heads than tiles of a workgroup; more than 8 splits
     (5, 5, 128, [513, 640, 1100]),                  # several panels; a tile group that ends inside a split
+    (4, 4, 64, [16, 17, 33, 48, 516, 1030]),        # plain heads, few rows: either kernel, alone and behind 4 and 8 splits
+    (4, 4, 128, [129, 300, 512, 529, 1032]),        # vector-ALU kernel up to 3 splits and for a few rows behind full panels
+    (8, 4, 128, [5, 8, 12, 520, 524]),
 ])
 def test_panel_attention_tile_edges(gpu, heads, kv_heads, head_dim, lengths):
     """Panel attention around the edges of a split (128 positions), a 16-row chunk, a workgroup's four tiles and a panel."""
@@ -182,9 +185,10 @@ def test_panel_attention_tile_edges(gpu, heads, kv_heads, head_dim, lengths):
 
 @pytest.mark.timeout(600)
 def test_panel_attention_with_fewer_partial_slots_than_items(gpu):
-    """1100 positions of 32 plain heads: 256 items per panel, room for the split partials of 223 workgroups."""
+    """32 plain heads: 256 items per 512-row panel.  The share sums' room holds the split partials of 2016 / (number of splits)
+    workgroups: 252 in the second panel of 1100 positions, 168 in the third of 1536."""
     s = synth.CONFIGS["7b"].with_(name="7b-1layer", n_layers=1, n_skip=0, gain_std=0.1)
-    _both_paths(gpu, s, [1100])
+    _both_paths(gpu, s, [1100, 1536])
 
 
 def test_tiled_weights_argument_errors(gpu, small_shapes):
