@@ -2,7 +2,6 @@
 // sequences behind the C-ABI declared in include/sdfp.h (paper Sec. II-A, Alg. 1 Stage B, Sec. III-C).
 #include "sdfp_kernels.hip.h"
 #include "sdfp_prefill.hip.h"
-#include "sdfp_prefill_plan.h"
 #include "sdfp.h"
 
 #include <algorithm>

@@ -28,6 +28,7 @@
 #pragma once
 #include <type_traits>
 #include "sdfp_attn.hip.h"
+#include "sdfp_prefill_plan.h"
 
 namespace sdfp {
 
@@ -626,8 +627,9 @@ struct PfAttnMx {
     int M, pos0;           // valid rows of the panel, absolute position of row 0
     LayerDims L;
 };
-constexpr int PFX_TILES = 4;                       // query tiles per workgroup
+constexpr int PFX_TILES = PF_MX_TILES;             // query tiles per workgroup
 constexpr int PFX_QUERIES = PFX_TILES * 16;
+static_assert(PF_CHUNK == MAX_ROWS && PF_SPLIT == ATT_SL, "the plan's cuts are the kernels'");
 __host__ __device__ constexpr size_t pfx_lds_bytes(int hd) { return (size_t)2 * 2 * ATT_SL * hd * 2; }   // 2 splits x (K, V)
 __host__ __device__ constexpr size_t pfx_slot_floats(int hd, int n_splits) { return (size_t)n_splits * PFX_QUERIES * (hd + 2); }
 
@@ -902,13 +904,15 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_pf_attn_mx(PfAttnMx a) {
         }
 
         // merge: the splits' partials weighted by exp(max_s - max) in ascending split order, four outputs per thread.  The
-        // statistics of as many queries as fit go to LDS first.
-        const int qb = min(PFX_QUERIES, max(1, (int)(pfx_lds_bytes(HD) / 8) / n_act_wg));
+        // statistics of as many queries as fit go to LDS first (none where one query's do not fit: a prompt of a million
+        // positions and more; they are read where they lie then).
+        const int fit = pf_mx_queries_in_lds((int)pfx_lds_bytes(HD), n_act_wg);
+        const int qb = fit > 0 ? fit : PFX_QUERIES;
         for (int q0 = 0; q0 < PFX_QUERIES; q0 += qb) {
             const int nqb = min(qb, PFX_QUERIES - q0);
             float2* stat = reinterpret_cast<float2*>(lds);   // [n_act_wg][qb]
             __syncthreads();      // also: every wave's partials are written
-            for (int e = tid; e < n_act_wg * nqb; e += WG_THREADS) {
+            for (int e = tid; e < n_act_wg * nqb && fit > 0; e += WG_THREADS) {
                 const int sI = e / nqb, ql = e - sI * nqb;
                 stat[sI * qb + ql] = *reinterpret_cast<const float2*>(slot_ml + ((size_t)sI * PFX_QUERIES + q0 + ql) * 2);
             }
@@ -919,8 +923,11 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_pf_attn_mx(PfAttnMx a) {
                 const int cq = tq / grp, m = cq * 16 + (qi & 15), hqq = g * grp + tq % grp;
                 if (m >= a.M) continue;
                 const int na = (chunk_end(cq) + ATT_SL - 1) / ATT_SL;
+                auto ml_of = [&](int sI) {
+                    return fit > 0 ? stat[sI * qb + ql] : *reinterpret_cast<const float2*>(slot_ml + ((size_t)sI * PFX_QUERIES + qi) * 2);
+                };
                 float gmax = -INFINITY;
-                for (int sI = 0; sI < na; ++sI) gmax = fmaxf(gmax, stat[sI * qb + ql].x);
+                for (int sI = 0; sI < na; ++sI) gmax = fmaxf(gmax, ml_of(sI).x);
                 const float* src = slot + (size_t)qi * HD + d0;
                 float num[4] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
                 for (int sb = 0; sb < na; sb += 8) {
@@ -931,7 +938,7 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_pf_attn_mx(PfAttnMx a) {
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
                         if (sb + k < na) {
-                            const float2 ml = stat[(sb + k) * qb + ql];
+                            const float2 ml = ml_of(sb + k);
                             const float w = (ml.x > -INFINITY) ? __expf(ml.x - gmax) : 0.f;
                             num[0] = fmaf(w, os[k].x, num[0]); num[1] = fmaf(w, os[k].y, num[1]);
                             num[2] = fmaf(w, os[k].z, num[2]); num[3] = fmaf(w, os[k].w, num[3]);

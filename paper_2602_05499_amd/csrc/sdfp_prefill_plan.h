@@ -13,6 +13,12 @@ struct PfAttnPanel {
 };
 constexpr int PF_CHUNK = 16, PF_SPLIT = 128, PF_MX_TILES = 4;   // rows of a chunk, positions of a split, tiles of a k_pf_attn_mx workgroup
 
+// Queries of a k_pf_attn_mx workgroup whose statistics, 8 bytes per split, its LDS holds at a time during the merge; 0: not one.
+constexpr int pf_mx_queries_in_lds(int lds_bytes, int n_splits) {
+    const int fit = lds_bytes / 8 / n_splits, all = PF_MX_TILES * PF_CHUNK;
+    return fit < all ? fit : all;
+}
+
 inline int pf_chunk_rows(const PfAttnPanel& p, int c) { return std::min(PF_CHUNK, p.M - c * PF_CHUNK); }
 inline int pf_chunk_splits(const PfAttnPanel& p, int c) {
     return (p.pos0 + c * PF_CHUNK + pf_chunk_rows(p, c) + PF_SPLIT - 1) / PF_SPLIT;

@@ -12,6 +12,7 @@ SHIM = """
 extern "C" int on_matrix_cores(int hd, int Hkv, int grp, int M, int pos0, int n_cu, int wg_valu, int wg_mx) {
     return sdfp::pf_attn_on_matrix_cores(sdfp::PfAttnPanel{hd, Hkv, grp, M, pos0, n_cu, wg_valu, wg_mx});
 }
+extern "C" int queries_in_lds(int lds_bytes, int n_splits) { return sdfp::pf_mx_queries_in_lds(lds_bytes, n_splits); }
 """
 # head_dim, KV heads, query heads per KV head, first position of the panel: [(rows, us of k_pf_attn, us of k_pf_attn_mx)]
 MEASURED = [
@@ -35,12 +36,17 @@ MEASURED = [
 
 
 @pytest.fixture(scope="module")
-def on_matrix_cores(tmp_path_factory):
+def plan(tmp_path_factory):
     d = tmp_path_factory.mktemp("prompt_plan")
     (d / "shim.cpp").write_text(SHIM)
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "shim.so"), str(d / "shim.cpp")],
                    check=True)
-    return ctypes.CDLL(str(d / "shim.so")).on_matrix_cores
+    return ctypes.CDLL(str(d / "shim.so"))
+
+
+@pytest.fixture(scope="module")
+def on_matrix_cores(plan):
+    return plan.on_matrix_cores
 
 
 @pytest.mark.parametrize("hd,n_kv,grp,pos0,times", MEASURED)
@@ -60,3 +66,12 @@ def test_the_choice_has_an_answer_at_the_limits(on_matrix_cores):
                             assert on_matrix_cores(hd, n_kv, grp, rows, pos0, n_cu, wg_valu, wg_mx) in (0, 1)
                 assert on_matrix_cores(hd, n_kv, grp, rows, 2048 * 128, 256, 512, 512) == 1   # no room for the other's merge
                 assert on_matrix_cores(hd, n_kv, grp, rows, 0, 256, 512, 0) == 0
+
+
+@pytest.mark.parametrize("lds_bytes", [64 * 1024, 128 * 1024])      # head_dim 64, 128
+def test_the_merge_statistics_never_exceed_the_lds(plan, lds_bytes):
+    """Also beyond a million positions, where those of a single query do not fit and none are staged."""
+    for n in list(range(1, 2000)) + [8191, 8192, 8193, 16383, 16384, 16385, 1 << 20]:
+        q = plan.queries_in_lds(lds_bytes, n)
+        assert 0 <= q <= 64 and q * n * 8 <= lds_bytes
+        assert q == 64 or (q + 1) * n * 8 > lds_bytes
