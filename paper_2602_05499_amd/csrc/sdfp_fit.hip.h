@@ -340,12 +340,15 @@ __global__ __launch_bounds__(256) void k_fit_transpose(const bf16_t* __restrict_
 // and holds D[rows 4 (l / 16) .. + 3][col l % 16]; a lane loads four consecutive k of its row at once, and which four k a
 // lane group takes does not matter as long as both operands take the same.  G is symmetric: only the 128 x 128 blocks on
 // and above the diagonal are computed (the others stay zero) and k_fit_dot counts a block above the diagonal twice. ----
+// Up to three matrices in one launch, a Gram matrix each (7B shape, 512 positions: 3 % of a call less than a launch each).
+// Adding them into one -- their products with one input's Gram matrix are linear -- would save a few more per cent, but the
+// scores are then twice as far from float64: 1.5e-7 instead of 7e-8.
 struct FitGramPart { const float* A; int w; };
 struct FitGram {
-    FitGramPart part[FIT_GRAM_PARTS];   // matrices [T][w] whose Gram matrices are added
-    int slice0[FIT_GRAM_PARTS + 1];     // first slice of each (blockIdx.y)
-    int n, k_per, T;                    // columns per slice
-    float* G;
+    FitGramPart part[FIT_GRAM_PARTS];   // matrices [T][w]
+    FitGramSlices s;                    // blockIdx.y counts the slices of all
+    int n, T;
+    float* G;                           // [n][T][T]
 };
 __global__ __launch_bounds__(256) void k_fit_gram(FitGram p) {
     // block (bi, bj), bi <= bj, of the upper triangle: blockIdx.x counts it column by column
@@ -353,14 +356,14 @@ __global__ __launch_bounds__(256) void k_fit_gram(FitGram p) {
     while ((bj + 1) * (bj + 2) / 2 <= (int)blockIdx.x) ++bj;
     const int bi = (int)blockIdx.x - bj * (bj + 1) / 2;
     int m = 0;
-    while (m + 1 < p.n && (int)blockIdx.y >= p.slice0[m + 1]) ++m;
+    while (m + 1 < p.n && (int)blockIdx.y >= p.s.slice0[m + 1]) ++m;
     const float* __restrict__ A = p.part[m].A;
-    float* __restrict__ G = p.G;
     const int w = p.part[m].w, T = p.T;
+    float* __restrict__ G = p.G + (size_t)m * T * T;
     // a workgroup owns a 128 x 128 block of G, wave (wr, wc) its 64 x 64 quarter: 4 + 4 operand loads feed 64 instructions
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, gq = lane >> 4;
     const int i0 = bi * 128 + (wave >> 1) * 64, j0 = bj * 128 + (wave & 1) * 64;
-    const int k_lo = ((int)blockIdx.y - p.slice0[m]) * p.k_per, k_hi = min(w, k_lo + p.k_per);
+    const int k_lo = ((int)blockIdx.y - p.s.slice0[m]) * p.s.k_per[m], k_hi = min(w, k_lo + p.s.k_per[m]);
     const float *ar[4], *br[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -412,11 +415,12 @@ __global__ __launch_bounds__(256) void k_fit_gram(FitGram p) {
         }
 }
 // *acc += sum_{t,t'} G1[t][t'] G2[t][t'] for two symmetric T x T matrices of which only the 128 x 128 blocks on and above
-// the diagonal are filled: a block above the diagonal stands for its mirror image as well
+// the diagonal are filled: a block above the diagonal stands for its mirror image as well.  blockIdx.y: one of several G2.
 __global__ __launch_bounds__(256) void k_fit_dot(const float* __restrict__ G1, const float* __restrict__ G2, int T, double* acc) {
     __shared__ float sh[16];
     float s = 0.f;
     const size_t n = (size_t)T * T;
+    G2 += blockIdx.y * n;
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
         const int i = (int)(e / T), j = (int)(e - (size_t)i * T), bi = i >> 7, bj = j >> 7;
         if (bj >= bi) s += (bj > bi ? 2.f : 1.f) * G1[e] * G2[e];

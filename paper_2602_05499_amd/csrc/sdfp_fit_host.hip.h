@@ -157,26 +157,34 @@ FitW fit_forward(const Fit& F, const void* W, int N, int K, int l, int slot) {
     }
     return FitW{dst, true};
 }
-// G = sum of the Gram matrices of up to three matrices
-void fit_gram(const Fit& F, std::initializer_list<FitGramPart> parts, float* G) {
+// the Gram matrices of up to three matrices, one behind the other from G on
+void fit_gram(const Fit& F, const FitGramPart* parts, int n, float* G) {
     const int T = F.D.T, tb = (T + 127) / 128, blocks = tb * (tb + 1) / 2;
-    (void)hipMemsetAsync(G, 0, (size_t)T * T * 4, F.st);
+    (void)hipMemsetAsync(G, 0, (size_t)n * T * T * 4, F.st);
     FitGram p;
     std::memset(&p, 0, sizeof(p));
-    p.T = T; p.G = G;
+    p.T = T; p.G = G; p.n = n;
     int w[FIT_GRAM_PARTS];
-    for (const FitGramPart& a : parts) { w[p.n] = a.w; p.part[p.n++] = a; }
-    const FitGramSlices sl = fit_gram_slices(T, w, p.n, F.n_cu);
-    p.k_per = sl.k_per;
-    std::memcpy(p.slice0, sl.slice0, sizeof(p.slice0));
-    hipLaunchKernelGGL(k_fit_gram, dim3(blocks, p.slice0[p.n]), dim3(256), 0, F.st, p);
+    for (int i = 0; i < n; ++i) { p.part[i] = parts[i]; w[i] = parts[i].w; }
+    p.s = fit_gram_slices(w, n);
+    hipLaunchKernelGGL(k_fit_gram, dim3(blocks, p.s.slice0[n]), dim3(256), 0, F.st, p);
 }
-// *acc += sum || dY^T X ||_F^2 over the gradients dY of the matrices that share the input X, whose Gram matrix is in GX:
-// the sum over the product with GX is linear, so their Gram matrices are added first
+void fit_input_gram(const Fit& F, const float* X, int w) {
+    const FitGramPart x{X, w};
+    fit_gram(F, &x, 1, F.f(F.cv.GX));
+}
+// *acc += || dY^T X ||_F^2 of each of the gradients dY of the matrices that share the input X, whose Gram matrix is in GX.
+// Together in one launch where the room of the share sums (idle here) holds their Gram matrices, else one by one.
 void fit_weight_norm(const Fit& F, std::initializer_list<FitGramPart> dYs, double* acc) {
-    float* GD = F.f(F.cv.GD);
-    fit_gram(F, dYs, GD);
-    hipLaunchKernelGGL(k_fit_dot, dim3(256), dim3(256), 0, F.st, F.f(F.cv.GX), GD, F.D.T, acc);
+    const FitDims& D = F.D;
+    const int n = (int)dYs.size(), T = D.T;
+    const bool together = n > 1 && (size_t)n * T <= (size_t)PF_NSHARE * std::max(D.d, D.hq);
+    float* G = F.f(together ? F.cv.shares : F.cv.GD);
+    for (int i = 0; i < n; i += together ? n : 1) {
+        const int m = together ? n : 1;
+        fit_gram(F, dYs.begin() + i, m, G);
+        hipLaunchKernelGGL(k_fit_dot, dim3(256, m), dim3(256), 0, F.st, F.f(F.cv.GX), G, T, acc);
+    }
 }
 
 template <bool AT, bool BT>
@@ -277,7 +285,7 @@ void fit_sample(const Fit& F, const sd_config* cfg, const sd_weights* w) {
 
     // ---- backward.  dh: gradient of the residual stream entering the part of the network still to be walked.
     float *dh = F.f(cv.dh), *dn = F.f(cv.dn), *dq = F.f(cv.dq), *dk = F.f(cv.dk), *dv = F.f(cv.dv), *datt = F.f(cv.datt);
-    float *dact = F.f(cv.dact), *dgt = F.f(cv.dgt), *dup = F.f(cv.dup), *dS = F.f(cv.dS), *GX = F.f(cv.GX);
+    float *dact = F.f(cv.dact), *dgt = F.f(cv.dgt), *dup = F.f(cv.dup), *dS = F.f(cv.dS);
     fit_gemm(F, fit_transposed(F, w->lm_head, D.V, D.d, L, 0), D.d, D.V, logits, nullptr, dn, D.d);
     hipLaunchKernelGGL(k_fit_rmsnorm_bwd, dim3(T), dim3(256), 0, F.st, hL, (const float*)w->final_norm, F.f(cv.rsf), dn, D.d,
                        (const float*)nullptr, dh);
@@ -289,13 +297,13 @@ void fit_sample(const Fit& F, const sd_config* cfg, const sd_weights* w) {
         double *s_attn = scores + l, *s_ffn = scores + L + l;
         // feed-forward sub-layer: h_out = x2 + act W_down^T
         hipLaunchKernelGGL(k_fit_swiglu, ew_grid(TF), dim3(256), 0, F.st, gt, up, TF, act);
-        fit_gram(F, {{act, D.F}}, GX);
+        fit_input_gram(F, act, D.F);
         fit_weight_norm(F, {{dh, D.d}}, s_ffn);                                              // w_down
         fit_gemm(F, fit_transposed(F, w->w_down[l], D.d, D.F, l, 6), D.F, D.d, dh, nullptr, dact, D.F);
         hipLaunchKernelGGL(k_fit_swiglu_bwd, ew_grid(TF), dim3(256), 0, F.st, dact, gt, up, TF, dgt, dup);
         hipLaunchKernelGGL(k_fit_rmsnorm, dim3(T), dim3(256), 0, F.st, x2, (const float*)w->ffn_norm[l], D.d, cfg->rms_eps, n, dn);
         // (the reciprocal RMS written to dn above is scratch: rs2 is the kept one)
-        fit_gram(F, {{n, D.d}}, GX);
+        fit_input_gram(F, n, D.d);
         fit_weight_norm(F, {{dgt, D.F}, {dup, D.F}}, s_ffn);                             // w_gate, w_up
         fit_gemm(F, fit_transposed(F, w->w_gate[l], D.F, D.d, l, 4), D.d, D.F, dgt, nullptr, dn, D.d);
         fit_gemm(F, fit_transposed(F, w->w_up[l], D.F, D.d, l, 5), D.d, D.F, dup, dn, dn, D.d);
@@ -303,14 +311,14 @@ void fit_sample(const Fit& F, const sd_config* cfg, const sd_weights* w) {
         hipLaunchKernelGGL(k_fit_rmsnorm_bwd, dim3(T), dim3(256), 0, F.st, x2, (const float*)w->ffn_norm[l], rs2, dn, D.d,
                            (const float*)dh, dh);                                        // dh = gradient at x2
         // attention sub-layer: x2 = x1 + att W_o^T
-        fit_gram(F, {{att, D.hq}}, GX);
+        fit_input_gram(F, att, D.hq);
         fit_weight_norm(F, {{dh, D.d}}, s_attn);                                             // wo
         fit_gemm(F, fit_transposed(F, w->wo[l], D.d, D.hq, l, 3), D.hq, D.d, dh, nullptr, datt, D.hq);
         fit_attention_bwd(F, datt, qr, kr, v, P, dS, dq, dk, dv);
         hipLaunchKernelGGL(k_fit_rope, dim3(T), dim3(256), 0, F.st, dq, D.H, D.hd, cosT, sinT, 1);
         hipLaunchKernelGGL(k_fit_rope, dim3(T), dim3(256), 0, F.st, dk, D.Hkv, D.hd, cosT, sinT, 1);
         hipLaunchKernelGGL(k_fit_rmsnorm, dim3(T), dim3(256), 0, F.st, x1, (const float*)w->attn_norm[l], D.d, cfg->rms_eps, n, dn);
-        fit_gram(F, {{n, D.d}}, GX);
+        fit_input_gram(F, n, D.d);
         fit_weight_norm(F, {{dq, D.hq}, {dk, D.hkv}, {dv, D.hkv}}, s_attn);              // wq, wk, wv
         fit_gemm(F, fit_transposed(F, w->wq[l], D.hq, D.d, l, 0), D.d, D.hq, dq, nullptr, dn, D.d);
         fit_gemm(F, fit_transposed(F, w->wk[l], D.hkv, D.d, l, 1), D.d, D.hkv, dk, dn, dn, D.d);

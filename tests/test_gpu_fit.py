@@ -110,6 +110,33 @@ def test_fit_scores_at_7b_width(gpu):
 
 
 @pytest.mark.timeout(900)
+def test_fit_scores_precision_at_7b_width(gpu):
+    """One layer of the benchmark's widths, 512 tokens: what float32 Gram matrices of 11008 columns give.  The error is that of
+    the sums along a slice of columns: 352 of them and a Gram matrix per gradient measure 7e-8 (runs differ by 5e-9), slices
+    twice as long, or the gate's and the up projection's gradients in one matrix, 1.5e-7.  And the gradients that share an
+    input at scales far apart (wq and wv 128, w_gate and w_up 256 times apart, the scores led by the larger): 3.2e-7, where
+    those measure 5.5e-7."""
+    import torch
+    from oracle.fit import fit_scores as reference
+    from paper_2602_05499_amd.session import fit_scores
+    from synth.device import DeviceWeights
+    s = synth.CONFIGS["7b"].with_(name="fit_7b_1layer", n_layers=1, n_skip=0, skip_layers=(), gain_std=0.1)
+    toks = [synth.gen_prompt(31, 512, s.vocab)]
+    for scale, bound in (({}, 1.1e-7), (dict(wq=1 / 16, wv=8.0, w_up=1 / 32, w_gate=8.0), 4.5e-7)):
+        dw = DeviceWeights(s)
+        for name, f in scale.items():
+            dw.layers[0][name].mul_(f)
+        torch.cuda.synchronize()
+        ra, rf, _ = reference(s, dw.to_host(), toks)
+        ta, tf, _ = fit_scores(s, dw, toks)
+        ea, ef = float(np.abs(ta - ra).max() / ra.max()), float(np.abs(tf - rf).max() / rf.max())
+        print(f"scaled {scale}: relative error attn {ea:.2e} ffn {ef:.2e}", flush=True)
+        assert ea <= bound and ef <= bound
+        del dw
+        torch.cuda.empty_cache()
+
+
+@pytest.mark.timeout(900)
 def test_fit_scores_on_the_benchmark_model(gpu):
     """All 32 layers of the 7B shape, a 512-token sequence (the configuration `bench.py --fit` times).  The oracle cannot
     form 32 layers of float64 weight gradients in test time, so what holds at any size is checked: scores finite and
