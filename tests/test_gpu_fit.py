@@ -1,7 +1,7 @@
 """FIT layer scores (Eq. 11; Alg. 1 Stage A) on the GPU against the oracle: the squared gradient norms of every layer's
 attention and feed-forward sub-layer over a small seeded calibration set, the samples' losses, and the prune set that
 follows from them.  The GPU works in float32 with bfloat16 weights taken exactly, the oracle in float64 on the same
-stored values: scores agree to a relative 1e-3 (asserted; what is measured is printed), losses to 1e-5."""
+stored values: scores agree to a relative 5e-6 (measured: 9e-7 at two positions, 6e-7 and less beyond), losses to 1e-5."""
 import ctypes
 
 import numpy as np
@@ -11,7 +11,7 @@ import synth
 
 pytestmark = pytest.mark.gpu
 
-RTOL_SCORE = 1e-3
+RTOL_SCORE = 5e-6
 ATOL_LOSS = 1e-5
 
 

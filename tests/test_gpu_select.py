@@ -2,13 +2,32 @@
 split: a row is cut into chunks of 512 entries, at most 256 of them, so one entry, one chunk with and without a remainder,
 the largest row of 256 full 512-entry chunks and the first row of longer chunks.  The rules of the oracle, evaluated on the
 logits rows the GPU itself produced, must give the GPU's tokens exactly (both sides sum in float64: only a uniform within
-about 1e-12 of a boundary could differ; the seeds below are checked not to come near one)."""
+about 1e-12 of a boundary could differ; every draw and test is checked to be 1e-10 away from its boundary)."""
 import numpy as np
 import pytest
 
 import synth
 
 pytestmark = pytest.mark.gpu
+
+
+def _off_boundary(w, u):
+    """The draw by u from weights w lies further than any float64 round-off from where it would give another entry."""
+    c = np.cumsum(np.asarray(w, np.float64))
+    return u == 0.0 or np.abs(c - u * c[-1]).min() > 1e-10 * c[-1]
+
+
+def _accept_off_boundary(d, zq, zp, u_acc, u_res, T):
+    """The same of a step's acceptance tests, up to the first rejection, and of its last draw."""
+    from oracle import softmax64
+    for i in range(len(d)):
+        p, q, t = softmax64(zp[i], T), softmax64(zq[i], T), int(d[i])
+        if p[t] == q[t] == 0.0 or float(u_acc[i]) * q[t] >= p[t]:
+            r = np.maximum(0.0, p - q)
+            return (p[t] == 0.0 or abs(float(u_acc[i]) * q[t] - p[t]) > 1e-10 * p[t]) and _off_boundary(r if r.sum() > 0.0 else p, u_res)
+        if abs(float(u_acc[i]) * q[t] - p[t]) <= 1e-10 * p[t]:
+            return False
+    return _off_boundary(softmax64(zp[len(d)], T), u_res)
 
 
 @pytest.mark.parametrize("vocab", [1, 2, 511, 512, 513, 1025, 32003, 131072, 131073, 200001])
@@ -27,6 +46,7 @@ def test_draws_and_accepts_follow_the_oracles_rules(vocab):
     u[1] = 0.0                       # the smallest uniform: the first entry with any weight
     ses.prefill(synth.gen_prompt(3, 7, vocab), P.SD_SAMPLE, u[:1])
     z = ses.dump_logits(P.SD_LOGITS_VERIFY, 1)[0]
+    assert _off_boundary(softmax64(z, T), u[0])
     assert ses.read()[1]["t_last"] == inv_cdf(softmax64(z, T), u[0])
     for i in range(n_steps):
         us = u[1 + i * (2 * K + 1):1 + (i + 1) * (2 * K + 1)]
@@ -37,16 +57,12 @@ def test_draws_and_accepts_follow_the_oracles_rules(vocab):
         ses.accept(P.SD_SAMPLE, us[K:])
         ses.rollback()
         st = ses.read()[1]
+        assert all(_off_boundary(softmax64(zq[j], T), us[j]) for j in range(K))
+        assert _accept_off_boundary(d, zq, zp, us[K:2 * K], float(us[2 * K]), T)
         assert [int(t) for t in d] == [inv_cdf(softmax64(zq[j], T), us[j]) for j in range(K)], i
         assert (st["last_n"], st["t_last"]) == accept_sample(d, zq, zp, us[K:2 * K], float(us[2 * K]), T), i
     ses.close()
     torch.cuda.synchronize()
-
-
-def _off_boundary(w, u):
-    """The draw by u from weights w lies further than any float64 round-off from where it would give another entry."""
-    c = np.cumsum(np.asarray(w, np.float64))
-    return u == 0.0 or np.abs(c - u * c[-1]).min() > 1e-10 * c[-1]
 
 
 @pytest.mark.parametrize("vocab,masked", [
@@ -102,7 +118,8 @@ def test_entries_of_minus_infinity_are_never_drawn(vocab, masked):
             st = ses.read()[1]
             if i % 2 and not draft_mask.any():
                 assert np.array_equal(zq[0], zp[0])           # the residual of row 0 is zero throughout
-                assert st["last_n"] == 0 and _off_boundary(softmax64(zp[0], T), float(us[2 * K]))
+                assert st["last_n"] == 0
+            assert _accept_off_boundary(d, zq, zp, us[K:2 * K], float(us[2 * K]), T)
             assert (st["last_n"], st["t_last"]) == accept_sample(d, zq, zp, us[K:2 * K], float(us[2 * K]), T), i
         ses.close()
     torch.cuda.synchronize()
