@@ -220,8 +220,8 @@ int sd_set_prefill_mode(sd_ctx *ctx, int mode);
 /* Optional, for the matrix-matrix prompt forward (Sec. II-A, "given input x"; bfloat16 storage): a second copy of
  * every layer's projection matrices in the order that path reads them -- per 16-row tile and 64-byte step of the
  * reduction dimension one contiguous kilobyte -- so that a step is a few whole cache lines instead of 64 separate
- * 16-byte accesses.  Same results bit for bit; the 512-token prompt of the 7B benchmark shape takes 22 ms with it
- * instead of 27, and the decode-time forwards, which read their O and down projections from it where d_model / 16
+ * 16-byte accesses.  Same results bit for bit; the 512-token prompt of the 7B benchmark shape takes 20 ms with it
+ * instead of 23, and the decode-time forwards, which read their O and down projections from it where d_model / 16
  * divides by the number of compute units, 1.5-2 % less (everything else they keep reading from the caller's matrices).
  * sd_tiled_weights_bytes: bytes of the copy (the size of the layer matrices; 0 for float32 storage or a bad cfg).
  * sd_set_tiled_weights: buf is DEVICE memory, 256-byte aligned, owned by the caller and borrowed until sd_free or

@@ -8,8 +8,8 @@
 // Arithmetic: weights are the stored bfloat16 values, every activation and gradient is float32.  Products with a weight
 // matrix (forward, and backward with respect to the input through a transposed copy of the matrix) run through the
 // prompt path's matrix-core GEMM (sdfp_prefill.hip.h: float32 activations as three bfloat16 pieces, float32
-// accumulation); Gram matrices through the float32 matrix-core instruction; attention, norms, rotary embedding, SwiGLU
-// and the cross-entropy on the vector ALUs.  Keys and values are not rounded: there is no cache in this pass.
+// accumulation); Gram matrices and the products of attention through the float32 matrix-core instruction; soft-max, norms,
+// rotary embedding, SwiGLU and the cross-entropy on the vector ALUs.  Keys and values are not rounded: there is no cache in this pass.
 #pragma once
 #include "sdfp_fit_plan.h"
 #include "sdfp_prefill.hip.h"
@@ -157,8 +157,8 @@ __global__ __launch_bounds__(256) void k_fit_bmm(FitBmm p) {
         const float* Bh = p.B + (size_t)(h / p.b_div) * p.b_hs;
         // Whole steps, operands loaded one step ahead of the instructions that use them (the last step loads itself again,
         // unused); without that every step waited out the latency of its loads (512 positions, 32 heads of 128: P V 121 us, now
-        // 46; P^T dO 95, now 38).  The ragged end, and operands whose rows
-        // do not allow the 16-byte loads, take the loop below.
+        // 46; P^T dO 95, now 38).  The ragged end takes the loop below, and so do operands whose rows do not allow the 16-byte
+        // loads: P and dS, of row pitch T, where T is no multiple of 4.
         int k_from = k_lo;
         if ((AT || va) && (!BT || vb) && k_lo + 16 <= min(k_hi, p.K)) {
             const int k_full = k_lo + (min(k_hi, p.K) - k_lo) / 16 * 16;

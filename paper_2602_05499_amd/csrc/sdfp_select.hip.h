@@ -13,7 +13,7 @@ struct Uni { float u[2 * MAX_K + 2]; };
 // each; the last one to arrive adds the chunks' sums in ascending order, finds the chunk in which the cumulative sum
 // crosses the target and scans that chunk alone.  (One kernel and a last-arriver counter instead of two kernels: the
 // counter costs less than the gap between two dependent launches.)  Measured at 32000 entries: a draw 73-89 -> 11 us, an
-// accept with K = 3 / 6 194 / 270 -> 19 us (statistics 5, the rest 14): what is left is latency, three dependent round
+// accept with K = 6 270 -> 22 us (statistics 5, the rest 17): what is left is latency, three dependent round
 // trips through memory and a few float64 exponentials.
 constexpr int SEL_THREADS = 256;
 constexpr int SEL_CHUNKS = SEL_THREADS;      // the last workgroup holds one chunk per thread
