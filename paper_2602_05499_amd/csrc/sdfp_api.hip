@@ -826,7 +826,7 @@ int do_prefill(sd_ctx* c, const int32_t* prompt_host, int n, int mode, const flo
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.counters),
                        c->cfg.n_kv_heads);
     const bool keep = mode == SD_SAMPLE || c->keep_logits;
-    const bool gemm = std::is_same<WT, bf16_t>::value && c->panel.P > 0 &&
+    const bool gemm = std::is_same<WT, bf16_t>::value && c->panel.P > 0 && pf_panels_hold(c->cfg.head_dim, n) &&
                       (c->prefill_mode == 1 || (c->prefill_mode < 0 && n >= PREFILL_MATRIX_MIN_ROWS));
     if (gemm) {
         HeadPlan hp{true, 0, keep ? c->f(c->cv.zp) : nullptr, ROWS_VERIFY, 0};

@@ -630,6 +630,8 @@ struct PfAttnMx {
 constexpr int PFX_TILES = PF_MX_TILES;             // query tiles per workgroup
 constexpr int PFX_QUERIES = PFX_TILES * 16;
 static_assert(PF_CHUNK == MAX_ROWS && PF_SPLIT == ATT_SL, "the plan's cuts are the kernels'");
+static_assert(PF_VALU_MAX_SPLITS * 8 <= attn_lds_bytes(16, 0, ATT_QC_PANEL, true) && PF_VALU_MAX_SPLITS * 8 <= attn_lds_bytes(32, 0, ATT_QC_PANEL, true) &&
+              PF_VALU_MAX_SPLITS * 8 <= attn_lds_bytes(64, 0, ATT_QC_PANEL, true), "one query's statistics fit k_pf_attn's LDS");
 __host__ __device__ constexpr size_t pfx_lds_bytes(int hd) { return (size_t)2 * 2 * ATT_SL * hd * 2; }   // 2 splits x (K, V)
 __host__ __device__ constexpr size_t pfx_slot_floats(int hd, int n_splits) { return (size_t)n_splits * PFX_QUERIES * (hd + 2); }
 

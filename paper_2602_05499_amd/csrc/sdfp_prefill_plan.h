@@ -78,8 +78,10 @@ inline double pf_mx_us(const PfAttnPanel& p) {
     }
     return worst;
 }
-// Beyond this many splits the other kernel's merge has no room in LDS for a query's statistics (head_dim 64: 2560).
-constexpr int PF_VALU_MAX_SPLITS = 2048;
+// The splits of which k_pf_attn's merge has room in LDS for one query's statistics: beyond them panels go to the other kernel,
+// or, at the head_dims it has no instance for, the prompt goes through the 16-row forward.
+constexpr int PF_VALU_MAX_SPLITS = 2560;
+inline bool pf_panels_hold(int hd, int n) { return hd >= 64 || (n + PF_SPLIT - 1) / PF_SPLIT <= PF_VALU_MAX_SPLITS; }
 inline bool pf_attn_on_matrix_cores(const PfAttnPanel& p) {
     if (p.wg_mx < 1) return false;
     return pf_chunk_splits(p, (p.M - 1) / PF_CHUNK) > PF_VALU_MAX_SPLITS || pf_mx_us(p) <= pf_valu_us(p);

@@ -12,6 +12,7 @@ SHIM = """
 extern "C" int on_matrix_cores(int hd, int Hkv, int grp, int M, int pos0, int n_cu, int wg_valu, int wg_mx) {
     return sdfp::pf_attn_on_matrix_cores(sdfp::PfAttnPanel{hd, Hkv, grp, M, pos0, n_cu, wg_valu, wg_mx});
 }
+extern "C" int panels_hold(int hd, int n) { return sdfp::pf_panels_hold(hd, n); }
 extern "C" int queries_in_lds(int lds_bytes, int n_splits) { return sdfp::pf_mx_queries_in_lds(lds_bytes, n_splits); }
 """
 # head_dim, KV heads, query heads per KV head, first position of the panel: [(rows, us of k_pf_attn, us of k_pf_attn_mx)]
@@ -64,7 +65,7 @@ def test_the_choice_has_an_answer_at_the_limits(on_matrix_cores):
                     for n_cu in (32, 256):
                         for wg_valu, wg_mx in ((1, 1), (8, 2), (512, 1), (512, 4096)):
                             assert on_matrix_cores(hd, n_kv, grp, rows, pos0, n_cu, wg_valu, wg_mx) in (0, 1)
-                assert on_matrix_cores(hd, n_kv, grp, rows, 2048 * 128, 256, 512, 512) == 1   # no room for the other's merge
+                assert on_matrix_cores(hd, n_kv, grp, rows, 2560 * 128, 256, 512, 512) == 1   # no room for the other's merge
                 assert on_matrix_cores(hd, n_kv, grp, rows, 0, 256, 512, 0) == 0
 
 
@@ -75,3 +76,11 @@ def test_the_merge_statistics_never_exceed_the_lds(plan, lds_bytes):
         q = plan.queries_in_lds(lds_bytes, n)
         assert 0 <= q <= 64 and q * n * 8 <= lds_bytes
         assert q == 64 or (q + 1) * n * 8 > lds_bytes
+
+
+def test_prompts_longer_than_the_vector_kernels_merge_leave_the_panels(plan):
+    """A workgroup of k_pf_attn has 20 KB of LDS at head_dim 16 and 32, 8 bytes per split: 2560 splits of 128 positions."""
+    for hd in (16, 32):
+        assert plan.panels_hold(hd, 5) and plan.panels_hold(hd, 2560 * 128) and not plan.panels_hold(hd, 2560 * 128 + 1)
+    for hd in (64, 128):
+        assert plan.panels_hold(hd, 1 << 24)
