@@ -79,16 +79,18 @@ bool config_ok(const sd_config* c) {
 
 inline size_t esize(const sd_config* c) { return c->dtype == SD_F32 ? 4 : 2; }
 
-// A turn of the register ring holds four 2 KB blocks of one 16-row tile.  The kernels whose turns may go on into the
-// next tile pay a few scalar operations per load for it, so they are used only where they gain: where the blocks of
-// a weight row do not fill whole turns and a workgroup has more than one tile of such rows to go on into.
+// A turn of the register ring holds four 2 KB blocks of one 16-row tile.  Two sets of decode kernels: in one the one-row
+// kernels run every slot of a turn as straight-line code, padding included; in the other a turn branches around blocks it
+// does not have and may go on into the next tile.  The second is the better one where rows of d_model values do not fill
+// whole turns -- QKV, gate/up and the output head read such rows (d 256 float32, one block: a step of 5 forwards 595 against
+// 545 us; d 5120 bfloat16, five blocks: 69 against 59 ms) -- or where the O / down projections' rows do not and a workgroup
+// has several tiles of them.  It costs a few scalar operations per load, 2 % where rows are whole turns (d 4096 bfloat16).
 inline bool span_pays(const sd_config* c, int n_wg) {
     const int turn = RING_MAX / SPW;
     auto ragged = [&](int Kd) { return (int)(((size_t)Kd * esize(c) + BLOCK_BYTES - 1) / BLOCK_BYTES) % turn != 0; };
-    const int hq = c->n_heads * c->head_dim, hkv = c->n_kv_heads * c->head_dim;
+    const int hq = c->n_heads * c->head_dim;
     const bool many_d_rows = c->d_model / 16 > n_wg;   // O and down projection: tiles per workgroup > 1
-    const bool many_x_rows = (hq + 2 * hkv) / 16 > n_wg || c->d_ffn / 8 > n_wg || c->vocab / 16 > n_wg;
-    return (ragged(c->d_model) && many_x_rows) || ((ragged(hq) || ragged(c->d_ffn)) && many_d_rows);
+    return ragged(c->d_model) || ((ragged(hq) || ragged(c->d_ffn)) && many_d_rows);
 }
 inline int n_splits(const sd_config* c) { return (c->max_seq + ATT_SL - 1) / ATT_SL; }
 inline size_t prog_len(const sd_config* c) { return (size_t)c->n_layers * 5 + 3; }
@@ -324,6 +326,15 @@ int forward_grid() {
     return n > HEAD_GRID_MAX ? HEAD_GRID_MAX : n;
 }
 
+void link_projections(std::vector<Phase>& prog) {   // Phase::link, from the end
+    int link = PK_END;
+    for (size_t i = prog.size(); i-- > 0;) {
+        prog[i].link = link;
+        const int k = prog[i].kind;
+        if (k == PK_QKV || k == PK_OPROJ || k == PK_GATEUP || k == PK_DOWN || k == PK_HEAD) link = ((int)i << 4) | k;
+    }
+}
+
 // The phase list of one forward: embedding, then for every layer the sub-layers that are not skipped, then
 // the output head.  A skipped sub-layer contributes nothing and writes no keys / values (Alg. 1: the draft is
 // the target minus the prune set); the residual stream simply passes to the next phase that runs.
@@ -401,6 +412,7 @@ std::vector<Phase> build_program(const sd_ctx* c, bool use_skip) {
         prog.push_back(p);
     }
     prog.push_back(blank(PK_END, -1));
+    link_projections(prog);
     return prog;
 }
 

@@ -115,7 +115,7 @@ struct Forward {
     __device__ __forceinline__ void sync_all(int kind, bool all_stored) {
         const bool service = wave == SERVICE_WAVE;
         if (all_stored) {
-            stores_done();
+            if (kind != PK_EMBED) stores_done();
             __syncthreads();
         }
         ++epoch;
@@ -123,7 +123,7 @@ struct Forward {
             if (!all_stored) stores_done();
             mark(kind * 2);
             if ((threadIdx.x & 63) == 0) {
-                bar_arrive(A.bar, epoch, wg, n_wg);
+                if (kind != PK_EMBED) bar_arrive(A.bar, epoch, wg, n_wg);   // (the embedding: arrived before the first weight loads)
                 bar_wait(A.bar, epoch, n_wg, A.spin_limit);
             }
         }
@@ -146,10 +146,11 @@ struct Forward {
 #endif
             st_coh4(p.out + idx, v);
         }
-        if constexpr (POLL) {   // arm the rows that are handed over by data: workgroup w takes phases w + 1, w + 1 + n_wg, ...
+        if constexpr (POLL) {   // arm the rows that are handed over by data: workgroup w takes phases n_wg - w, 2 n_wg - w, ... (the
+                                // first workgroups have the embedding rows to fetch)
             const unsigned a = HANDOVER_ARMED;
             const f32x4 armed = {__uint_as_float(a), __uint_as_float(a), __uint_as_float(a), __uint_as_float(a)};
-            for (int ph = 1 + wg; ph < A.n_prog; ph += n_wg) {
+            for (int ph = n_wg - wg; ph < A.n_prog; ph += n_wg) {
                 const SDFP_CONST Phase* q = as_const(A.prog) + ph;
                 const int k = q->kind;
                 if (k != PK_ATTN && k != PK_OPROJ && k != PK_GATEUP && k != PK_DOWN) continue;
@@ -202,6 +203,22 @@ struct Forward {
         n_trace = 0;
         mark(0);
 
+        // The embedding comes before any weight load: its chain (descriptor and token, table row, store, acknowledgement)
+        // is made of loads that would return behind the 16 weight loads of a ring, under a full memory system.  The first
+        // turn of weights is fetched while the grid barrier after the embedding is waited for (12.4 -> 9.0 us from the start
+        // of a launch to the first projection, 7B shape).
+        const Phase p0 = load_phase(A.prog, 0);
+        const bool has_embed = p0.kind == PK_EMBED;
+        if (has_embed) embed(p0);   // (the list that holds the output head alone has none)
+        {   // The descriptor of every phase is read with scalar loads that start out cold, in the chain between two projections:
+            // the workgroups of an XCD (id % 8) bring the list's cache lines into its L2 now, a few each.
+            const int n_line = (A.n_prog * (int)sizeof(Phase) + 127) >> 7, per_xcd = (n_wg + 7) >> 3;
+            const int line = (wg >> 3) + (int)threadIdx.x * per_xcd;
+            if (line < n_line) {
+                const int touched = *(const SDFP_GLOBAL int*)((const char*)A.prog + (size_t)line * 128);
+                asm volatile("" ::"v"(touched));
+            }
+        }
         // this workgroup's geometry of every projection kind, kept in LDS for the whole launch
         if (threadIdx.x < LDS_ZERO_BYTES / 4) reinterpret_cast<float*>(lds + LDS_ZERO_OFF)[threadIdx.x] = 0.f;
         if (threadIdx.x < 8) {
@@ -209,19 +226,20 @@ struct Forward {
             const int k = threadIdx.x;
             if (is_projection(k)) *gt = make_geom<WT>(k, A.kind_units[k], A.kind_Kd[k], phase_rows(k, M, A.head_row_from), wg, n_wg);
         }
+        stores_done();
         __syncthreads();
         SDFP_BEACON(2);
+        if (has_embed && threadIdx.x == SERVICE_WAVE * 64) bar_arrive(A.bar, 1u, wg, n_wg);   // waited for in the loop
         Loader<WT, RD, SPAN> ld;
         ld.init(A.prog, lds, A.L, A.head_run, wave, wave == SERVICE_WAVE ? HOLD : 0);
         SDFP_BEACON(3);
         Ring<RD> ring;
-        {
+        {   // (the service wave's loader starts on hold: its loads re-read a cached line)
             const Turn t0 = ld.next_turn();
 #pragma unroll
             for (int j = 0; j < RD; ++j) ring.r[j] = ld.load(t0, j);
         }
         SDFP_BEACON(4);
-
         for (int ph = 0;; ++ph) {
             Phase p = load_phase(A.prog, ph);
             SDFP_BEACON(1000 + ph * 10 + p.kind);
@@ -232,7 +250,7 @@ struct Forward {
             if (p.kind == PK_END || (p.kind == PK_HEAD && !A.head_run)) break;
             const bool all_stored = p.kind == PK_EMBED || p.kind == PK_ATTN;
             if (p.kind == PK_EMBED) {
-                embed(p);
+                // done above; only the wait for the grid barrier is left
             } else if (p.kind == PK_ATTN) {
 #ifndef SDFP_NO_ATTN
                 attention(p);

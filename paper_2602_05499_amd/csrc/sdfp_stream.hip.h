@@ -16,8 +16,13 @@
 // activation), for f32 weights as float32.  When M rows of the reduction length do not fit in LDS the block is
 // staged in activation tiles of KT8 blocks and the partial sums are carried in LDS between them.
 //
-// Every wave keeps RD (16, for prompt chunks 8) loads in flight in a register ring; a TURN of the ring is RD / 4
-// blocks x 4 steps of one tile, set up once (all per-item cost is a clamp and an add).  The loader runs one turn
+// Every wave keeps RD (16, for prompt chunks 8) loads in flight in a register ring; a TURN of the ring is up to RD / 4
+// blocks x 4 steps of one tile, set up once (all per-item cost is a clamp and an add).  Blocks that a turn does not have
+// are neither loaded nor multiplied, and the activation operand of a step is read from LDS while the one before it is
+// multiplied (read and used back to back, a turn of 16 steps took 3.4 us even with its weights in registers): a phase of
+// one short turn streams in 1.0-1.5 us, 3.6 with padding, and five rows' activation tiles of ragged length (down
+// projection of the 7B shape) in 18.2, 20.3 with it.  The one-row kernels of rows that fill whole turns are the exception
+// (STRAIGHT): they are bound by memory either way, and the branches cost them 1 %.  The loader runs one turn
 // ahead of the consumer over tile, group and PHASE boundaries (the weight addresses of later phases depend on no
 // activation), so a phase starts with its first turn already in registers.  Load issue is throttled by the
 // memory system (under load a turn takes one memory latency, 4-5 us, whether or not its data was prefetched), so
@@ -72,7 +77,7 @@ struct Phase {
     int Kd;             // reduction length (projection kinds)
     int N;              // output features of the projection (QKV: (H + 2 Hkv) * hd; gate/up: F)
     int n_units;        // distribution units: QKV blocks of 8 rotary pairs, gate/up pairs, else output rows
-    int pad_;
+    int link;           // the next projection phase of the list: (its index << 4) | its kind; PK_END past the last one
     const void* wt;     // the projection's matrices once more in tile order (tile t, step s -> one kilobyte, lane l's
                         // 16 bytes of the A operand at l * 16), or nullptr.  Only set where every workgroup's tiles are
                         // whole tiles of that numbering (O / down when N / 16 divides by the grid size; QKV could be).
@@ -90,7 +95,7 @@ __device__ __forceinline__ Phase load_phase(const Phase* prog, int ph) {
     const SDFP_CONST Phase* q = as_const(prog) + ph;   // member by member: each access keeps its own type
     Phase p;
     p.kind = q->kind; p.layer = q->layer; p.Kd = q->Kd; p.N = q->N; p.n_units = q->n_units;
-    p.pad_ = 0; p.wt = q->wt;
+    p.link = 0; p.wt = q->wt;
     p.w[0] = q->w[0]; p.w[1] = q->w[1]; p.w[2] = q->w[2];
     p.gain = q->gain; p.xin = q->xin; p.res = q->res; p.out = q->out;
     p.kc = q->kc; p.vc = q->vc;
@@ -198,7 +203,7 @@ struct Turn {
     const char* rowp;       // per lane: its row of the (first) tile + 16 * (lane / 16)
     const char* rowp2;      // the same for the second tile (== rowp when the turn has one segment)
     int nA;                 // blocks of the first segment
-    int span;               // 1 if there is a second segment
+    int nb;                 // blocks of both segments
     int off0, lim;          // first segment
     int off2, lim2;         // second segment (a copy of the first when there is none: padding re-reads it)
     int sh;                 // log2 of the bytes of the matrix per byte of offset: 0 row-major (an offset is a byte of the
@@ -221,6 +226,7 @@ struct Loader {
     int hd, H, Hkv;
     int head_run, wave;
     int ph, kind;                 // phase the loader is in; PK_END once the list is exhausted
+    int link;                     // the projection phase after it (see Phase)
     int pitch;                    // bytes per weight row
     int hold;                     // service wave: 1 = stop at every phase end until release(), 2 = only after a QKV phase
                                   // (where a grid barrier follows and its stores have to be waited for)
@@ -277,7 +283,9 @@ struct Loader {
     // move to the next projection phase that has tiles for this workgroup
     __device__ __forceinline__ void next_phase() {
         for (;;) {
-            ++ph;
+            ph = link >> 4; kind = link & 15;
+            if (kind == PK_HEAD && !head_run) kind = PK_END;
+            if (kind == PK_END) return;
 #ifdef SDFP_GUARD
             if ((const void*)prog != s_guard.prog || ph < 0 || ph >= s_guard.prog_len) {   // never walk off the list
                 guard_fail(prog + ph, ph, 50);
@@ -285,25 +293,24 @@ struct Loader {
                 return;
             }
 #endif
+            // everything the loader wants of the descriptor in one round trip
             const SDFP_CONST Phase* p = as_const(prog) + ph;
-            kind = p->kind;
-            if (kind == PK_HEAD && !head_run) kind = PK_END;
-            if (kind == PK_END) return;
-            if (!is_projection(kind)) continue;
+            link = p->link;
+            pitch = p->Kd * (int)sizeof(WT); n_rows = p->N;
+            wt = (const char*)p->wt;
+            w0 = (const char*)p->w[0];
+            const char* w1 = (const char*)p->w[1];
             const Geom* g = reinterpret_cast<const Geom*>(lds + LDS_GEOM_OFF) + kind;
             nt = __builtin_amdgcn_readfirstlane(g->nt);
-            if (nt <= 0) continue;
             u0 = __builtin_amdgcn_readfirstlane(g->u0);
             u1 = __builtin_amdgcn_readfirstlane(g->u1);
             S = __builtin_amdgcn_readfirstlane(g->S);
             nblk = __builtin_amdgcn_readfirstlane(g->nblk);
             KT8 = __builtin_amdgcn_readfirstlane(g->KT8);
             TG = __builtin_amdgcn_readfirstlane(g->TG);
-            pitch = p->Kd * (int)sizeof(WT); n_rows = p->N;
-            wt = (const char*)p->wt;
+            if (nt <= 0) continue;
             const bool gu = kind == PK_GATEUP;
-            w0 = (const char*)p->w[0];
-            whi = (const char*)p->w[gu ? 1 : 0]; tmul = gu ? 8 : 16; hioff = gu ? 0 : 8;
+            whi = gu ? w1 : w0; tmul = gu ? 8 : 16; hioff = gu ? 0 : 8;
             grp0 = 0;
             set_group();
             set_tile();
@@ -318,6 +325,8 @@ struct Loader {
         ph = -1; kind = PK_HOLD;
         rowp = (const char*)prog_; mat_lo = nullptr; mat_hi = nullptr; n_probe = 0;
         S = 1; kt0 = 0; c = 0; kt_n = 1; grp_n = 1; t = 0; nblk = 1; KT8 = 1; TG = 1; nt = 0; grp0 = 0;
+        const SDFP_CONST Phase* p0 = as_const(prog_);
+        link = is_projection(p0->kind) ? p0->kind : p0->link;   // (index 0 is in the bits above)
         if (!hold) next_phase();
     }
     // service wave: step from a phase end (or the start of the list) into the next phase with work
@@ -354,21 +363,21 @@ struct Loader {
     __device__ __forceinline__ Turn next_turn() {
         Turn tr;
         if (kind == PK_END || kind == PK_HOLD) {
-            tr.rowp = tr.rowp2 = (const char*)prog; tr.nA = TURN_BLOCKS; tr.span = 0; tr.off0 = tr.off2 = 0; tr.lim = tr.lim2 = 0;
+            tr.rowp = tr.rowp2 = (const char*)prog; tr.nA = TURN_BLOCKS; tr.nb = 0; tr.off0 = tr.off2 = 0; tr.lim = tr.lim2 = 0;
             tr.sh = 0;
             tr.lo = tr.lo2 = (const char*)prog; tr.hi = tr.hi2 = (const char*)prog + 16;
             return tr;
         }
         const int nbA = min(TURN_BLOCKS, kt_n - c);
         tr.rowp = rowp; tr.lo = mat_lo; tr.hi = mat_hi;
-        tr.nA = nbA; tr.span = 0; tr.sh = wt != nullptr ? 4 : 0;
+        tr.nA = nbA; tr.nb = nbA; tr.sh = wt != nullptr ? 4 : 0;
         tr.off0 = (kt0 + c) * BLOCK_BYTES + wave * (SPW * STEP_BYTES);
         tr.lim = min((S - 1) * STEP_BYTES, tr.off0 + (nbA - 1) * BLOCK_BYTES + (SPW - 1) * STEP_BYTES);
         tr.rowp2 = tr.rowp; tr.off2 = tr.off0; tr.lim2 = tr.lim; tr.lo2 = tr.lo; tr.hi2 = tr.hi;
         c += nbA;
         if (c >= kt_n && next_tile() && SPAN && nbA < TURN_BLOCKS) {   // the turn goes on into the next tile
             const int nbB = min(TURN_BLOCKS - nbA, kt_n);
-            tr.span = 1;
+            tr.nb = nbA + nbB;
             tr.rowp2 = rowp; tr.lo2 = mat_lo; tr.hi2 = mat_hi;
             tr.off2 = kt0 * BLOCK_BYTES + wave * (SPW * STEP_BYTES);
             tr.lim2 = min((S - 1) * STEP_BYTES, tr.off2 + (nbB - 1) * BLOCK_BYTES + (SPW - 1) * STEP_BYTES);
@@ -409,9 +418,17 @@ struct Loader {
 };
 
 // ---- matrix-core step: acc[16 rows][16 columns] += W step (A) x activation step (B) ------------------------
+// The B operand (NX 16-byte quads per lane) is fetched from LDS apart from its use, so that a caller can read the next
+// step's while this one is multiplied.
 template <typename WT> struct Mma;
 template <> struct Mma<bf16_t> {
-    static __device__ __forceinline__ void run(f32x4& acc, const u32x4& a, const char* xl, int piece_stride) {
+    static constexpr int NX = NSPLIT;
+    static __device__ __forceinline__ void fetch(u32x4 (&x)[NX], const char* xl, int piece_stride) {
+#pragma unroll
+        for (int s = 0; s < NSPLIT; ++s)
+            x[s] = *reinterpret_cast<const u32x4*>(__builtin_assume_aligned(xl + s * piece_stride, 16));
+    }
+    static __device__ __forceinline__ void fetch_run(f32x4& acc, const u32x4& a, const char* xl, int piece_stride) {
         const bf16x8 av = __builtin_bit_cast(bf16x8, a);
 #pragma unroll
         for (int s = 0; s < NSPLIT; ++s) {
@@ -419,14 +436,28 @@ template <> struct Mma<bf16_t> {
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
         }
     }
+    static __device__ __forceinline__ void run(f32x4& acc, const u32x4& a, const u32x4 (&x)[NX]) {
+        const bf16x8 av = __builtin_bit_cast(bf16x8, a);
+#pragma unroll
+        for (int s = 0; s < NSPLIT; ++s)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, x[s]), acc, 0, 0, 0);
+    }
 };
 template <> struct Mma<float> {
-    static __device__ __forceinline__ void run(f32x4& acc, const u32x4& a, const char* xl, int) {
-        const f32x4 b = *reinterpret_cast<const f32x4*>(__builtin_assume_aligned(xl, 16));
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), b.x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), b.y, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), b.z, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), b.w, acc, 0, 0, 0);
+    static constexpr int NX = 1;
+    static __device__ __forceinline__ void fetch(u32x4 (&x)[NX], const char* xl, int) {
+        x[0] = *reinterpret_cast<const u32x4*>(__builtin_assume_aligned(xl, 16));
+    }
+    static __device__ __forceinline__ void fetch_run(f32x4& acc, const u32x4& a, const char* xl, int) {
+        u32x4 x[NX];
+        fetch(x, xl, 0);
+        run(acc, a, x);
+    }
+    static __device__ __forceinline__ void run(f32x4& acc, const u32x4& a, const u32x4 (&x)[NX]) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(x[0].x), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(x[0].y), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(x[0].z), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(x[0].w), acc, 0, 0, 0);
     }
 };
 
@@ -465,6 +496,7 @@ template <typename WT, int ROWS, int RD, bool POLL, bool SPAN>
 struct Projection {
     static constexpr int TURN_BLOCKS = RD / SPW;
     static constexpr int XROWS = XGeo<WT>::XROWS;
+    static constexpr bool STRAIGHT = ROWS == 1 && !SPAN;
     const Phase& p;
     const LayerDims& L;
     char* lds;
@@ -827,8 +859,13 @@ struct Projection {
             ld.release();
             const Turn t0 = ld.next_turn();
 #pragma unroll
-            for (int j = 0; j < RD; ++j) ring.r[j] = ld.load(t0, j);
+            for (int j = 0; j < RD; ++j) 
+                if (STRAIGHT || j / SPW < t0.nb) ring.r[j] = ld.load(t0, j);
         }
+        // The turn that follows the one in the ring.  The loader steps ahead of its use: crossing into the next phase reads
+        // that phase's descriptor (a chain of scalar loads), which belongs into the wait for the input rows and not between
+        // their arrival and the phase's first matrix-core step.
+        Turn nx = ld.next_turn();
         if (kind == PK_HEAD && threadIdx.x < 16) {
             lds_f(LM_BESTV)[threadIdx.x] = -INFINITY;
             reinterpret_cast<int*>(lds + LM_BESTI)[threadIdx.x] = 0x7FFFFFFF;
@@ -879,27 +916,49 @@ struct Projection {
                     const int nbA = min(TURN_BLOCKS, kt_n - c);
                     const bool more = SPAN && c + nbA >= kt_n && tl + 1 < grp_n && nbA < TURN_BLOCKS;
                     const int nbB = more ? min(TURN_BLOCKS - nbA, kt_n) : 0;
-                    const Turn nx = ld.next_turn();
-                    // consume slot j, THEN refill it: the new load may then target the same registers, so the
-                    // ring needs no copy at the end of the turn.  The generated code waits once, at the top of the
-                    // turn, for the 16 loads issued during the previous turn and then runs through the slots; with
-                    // two waves per SIMD and 8 per workgroup that keeps enough loads in flight to stream at the
-                    // memory's rate (a build with a third of the matrix-core work per slot streams no faster).
+                    // Consume a slot, THEN refill it: the new load may then target the same registers, so the ring needs no
+                    // copy at the end of the turn.
+                    if constexpr (STRAIGHT) {
+                        // One row and rows of whole turns: every slot goes through the matrix core, without a branch.  A slot
+                        // that holds no block of the tile (its load re-read an earlier line) is multiplied by a block of
+                        // zeros kept in LDS.
 #pragma unroll
-                    for (int j = 0; j < RD; ++j) {
-                        const int b = j / SPW;
-                        if (j % SPW == 0 && b > 0 && b == nbA && nbB > 0) {   // the next tile starts with this block
-                            tile_store(tl, acc);
-                            acc = tile_init(tl + 1);
+                        for (int j = 0; j < RD; ++j) {
+                            const int b = j / SPW;
+                            const bool real = b < nbA;
+                            const char* xp = real ? xl + (c + b) * BLOCK_BYTES : xz;
+                            Mma<WT>::fetch_run(acc, ring.r[j], xp + (j % SPW) * STEP_BYTES, real ? piece_stride : 0);
+                            ring.r[j] = ld.load(nx, j);
                         }
-                        // Every slot goes through the matrix core, without a branch (a branch would split the turn
-                        // into pieces that each wait for all outstanding loads).  A slot that holds no block of the
-                        // tile (its load re-read an earlier line) is multiplied by a block of zeros kept in LDS.
-                        const int xb = b < nbA ? c + b : b - nbA;   // block of the activation tile
-                        const bool real = b < nbA + nbB;
-                        const char* xp = real ? xl + xb * BLOCK_BYTES : xz;
-                        Mma<WT>::run(acc, ring.r[j], xp + (j % SPW) * STEP_BYTES, real ? piece_stride : 0);
-                        ring.r[j] = ld.load(nx, j);
+                    } else {
+                    // All of the turn's loads are waited for at once, here: what follows then waits for no memory, whatever
+                    // branches it takes.  Blocks that the turn or its successor does not have are branched around: a padding
+                    // load costs the first-level cache as much as any other (a row-major step is 64 accesses, a turn of 8
+                    // waves 8192 cycles of it, 3.6 us).
+                    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+                    const int nb = nbA + nbB;
+#pragma unroll
+                    for (int b = 0; b < TURN_BLOCKS; ++b) {
+                        if (b < nb) {
+                            if (SPAN && b > 0 && b == nbA) {   // the next tile starts with this block
+                                tile_store(tl, acc);
+                                acc = tile_init(tl + 1);
+                            }
+                            const char* xp = xl + (b < nbA ? c + b : b - nbA) * BLOCK_BYTES;
+                            u32x4 x[2][Mma<WT>::NX];
+                            Mma<WT>::fetch(x[0], xp, piece_stride);
+#pragma unroll
+                            for (int i = 0; i < SPW; ++i) {   // the next step's operand on its way while one is multiplied
+                                if (i + 1 < SPW) Mma<WT>::fetch(x[(i + 1) & 1], xp + (i + 1) * STEP_BYTES, piece_stride);
+                                __builtin_amdgcn_sched_barrier(0);
+                                Mma<WT>::run(acc, ring.r[b * SPW + i], x[i & 1]);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                        }
+                        if (b < nx.nb)
+#pragma unroll
+                            for (int i = 0; i < SPW; ++i) ring.r[b * SPW + i] = ld.load(nx, b * SPW + i);
+                    }
                     }
 #ifdef SDFP_WAVETRACE
                     mark(17);
@@ -910,6 +969,7 @@ struct Projection {
                         ++tl; c = 0;
                         if (tl < grp_n) acc = tile_init(tl);
                     }
+                    if (tl < grp_n || kt0 + kt_n < g.nblk || grp0 + grp_n < g.nt) nx = ld.next_turn();   // not the phase's last
                 }
                 SDFP_BEACON2(12 + kt0 * 100 + grp0 * 100000);
             }
