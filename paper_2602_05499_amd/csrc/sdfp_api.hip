@@ -19,7 +19,7 @@ using namespace sdfp;
 // The forward kernels are instantiated in the sdfp_fwd_<type>_hd<n>.hip translation units: per storage type and
 // head_dim, one for prompt chunks, one draft row, one plain decode row, and one verify kernel per row count 2..9.
 namespace sdfp {
-#define SDFP_DECL(WT, ROLE, LPP, M, SPAN, LC) extern template __global__ void k_forward<WT, ROLE, LPP, M, SPAN, LC>(FwdArgs);
+#define SDFP_DECL(WT, ROLE, LPP, M, SPAN, LC) extern template __global__ void k_forward<WT, ROLE, LPP, M, SPAN>(FwdArgs);
 #define SDFP_DECL_DECODE(WT, LPP, SPAN, LC)                                                                       \
     SDFP_DECL(WT, 1, LPP, 1, SPAN, LC) SDFP_DECL(WT, 3, LPP, 1, SPAN, LC)                                          \
     SDFP_DECL(WT, 2, LPP, 2, SPAN, LC) SDFP_DECL(WT, 2, LPP, 3, SPAN, LC) SDFP_DECL(WT, 2, LPP, 4, SPAN, LC)       \
@@ -42,7 +42,7 @@ namespace {
 enum StepState { PH_INIT = 0, PH_READY, PH_DRAFTED, PH_VERIFIED, PH_ACCEPTED };
 
 struct Carve {   // byte offsets inside the workspace
-    size_t state, out_tokens, prompt, cosT, sinT, acts, part_o, part_ml, counters, zq, zp, head_val, head_idx,
+    size_t state, out_tokens, prompt, cosT, sinT, acts, part_o, part_ml, zq, zp, head_val, head_idx,
         prog_target, prog_draft, prog_head, bar, trace, guard_rec, total;
     size_t act_h, act_q, act_a;   // bytes of one residual / query / feed-forward activation block
     size_t acts_bytes;            // bytes of the activation region (also the scratch of the matrix-matrix prompt path)
@@ -100,7 +100,7 @@ inline size_t prog_len(const sd_config* c) { return (size_t)c->n_layers * 5 + 3;
 struct PanelPlan {
     int P;                 // rows per panel (a multiple of 64), 0 = the path is not available for this configuration
     int n_awg;             // workgroups of the panel's attention kernel (each owns a region of split partials)
-    size_t h_last, h, q, att, rs, xs_a, xs_b, shares, part, counters;
+    size_t h_last, h, q, att, rs, xs_a, xs_b, shares, part;
     size_t part_stride;    // floats per attention workgroup region
     size_t part_ml_off;    // floats from a region's start to its (max, sum) pairs
     int Ka;                // row length of xs_a: max(d_model, n_heads * head_dim)
@@ -145,7 +145,6 @@ PanelPlan plan_panel(const sd_config* c, size_t region_bytes) {
             pl.rs = take((size_t)P * 4);
             pl.xs_a = take((size_t)3 * P * pl.Ka * 2); pl.xs_b = take((size_t)3 * P * F * 2);
             pl.shares = take((size_t)PF_NSHARE * P * d * 4);
-            pl.counters = take(PANEL_MAX_AWG * 4);
             pl.part = take((size_t)pl.n_awg * region);
             if (off > region_bytes) { pl.P = 0; continue; }
             return pl;
@@ -184,7 +183,7 @@ Carve carve(const sd_config* c, bool compact = false) {
     k.acts = take(k.acts_bytes);
     k.part_o = take(sizeof(float) * (size_t)n_splits(c) * MAX_ROWS * dq);
     k.part_ml = take(sizeof(float) * (size_t)n_splits(c) * MAX_ROWS * c->n_heads * 2);
-    k.counters = take(sizeof(unsigned) * (size_t)c->n_kv_heads);
+    take(sizeof(unsigned) * (size_t)c->n_kv_heads);   // not used; the sizes that callers' buffers were made for stay what they were
     k.zq = take(sizeof(float) * (size_t)(c->max_k > 0 ? c->max_k : 1) * c->vocab);
     k.zp = take(sizeof(float) * (size_t)(c->max_k + 1) * c->vocab);
     k.head_val = take(sizeof(float) * HEAD_GRID_MAX * MAX_ROWS);   // (the selection kernels' buffers too, see sd_ctx::sel)
@@ -458,8 +457,6 @@ int lazy_device_init(sd_ctx* c) {
     std::memset(&z, 0, sizeof(z));
     z.max_out = g.max_out;
     HIPCHK(c, hipMemcpyAsync(c->st(), &z, sizeof(z), hipMemcpyHostToDevice, c->stream));
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(256), 0, c->stream,
-                       reinterpret_cast<unsigned*>(c->ws + c->cv.counters), g.n_kv_heads);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.bar), BAR_WORDS + 1);
     // the diagnostics' records start empty whatever the workspace held before
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream,
@@ -502,7 +499,6 @@ int forward(sd_ctx* c, Rows rows, int which, HeadPlan hp) {
     A.tok_emb = c->tok_emb;
     A.cosT = c->f(c->cv.cosT); A.sinT = c->f(c->cv.sinT);
     A.part_o = c->f(c->cv.part_o); A.part_ml = c->f(c->cv.part_ml);
-    A.att_counters = reinterpret_cast<unsigned*>(c->ws + c->cv.counters);
     A.head.logits = hp.logits;
     A.head.part_val = c->f(c->cv.head_val);
     A.head.part_idx = reinterpret_cast<int*>(c->ws + c->cv.head_idx);
@@ -548,32 +544,26 @@ int forward(sd_ctx* c, Rows rows, int which, HeadPlan hp) {
     // outside prompt chunks the rows are handed over by data, and the row that readers poll is row 0 of a buffer:
     // the output head must start at row 0 there (it does: draft, verify and plain decode take logits of every row)
     if (role != 0 && hp.run && hp.row_from != 0) return SD_EINVAL;
-    // contexts of more than 8 attention splits are possible: the instances that hold the merge of many splits
-    const bool long_ctx = n_splits(&c->cfg) > 8;
-#define SDFP_LAUNCH_ROWS(LPP, SPAN, LC)                                   \
+#define SDFP_LAUNCH_ROWS(LPP, SPAN)                                   \
     switch (role) {                                                      \
-        case 1: return launch(k_forward<WT, 1, LPP, 1, SPAN, LC>);         \
-        case 3: return launch(k_forward<WT, 3, LPP, 1, SPAN, LC>);         \
+        case 1: return launch(k_forward<WT, 1, LPP, 1, SPAN>);         \
+        case 3: return launch(k_forward<WT, 3, LPP, 1, SPAN>);         \
         default:                                                         \
             switch (rows.M) {                                            \
-                case 2: return launch(k_forward<WT, 2, LPP, 2, SPAN, LC>); \
-                case 3: return launch(k_forward<WT, 2, LPP, 3, SPAN, LC>); \
-                case 4: return launch(k_forward<WT, 2, LPP, 4, SPAN, LC>); \
-                case 5: return launch(k_forward<WT, 2, LPP, 5, SPAN, LC>); \
-                case 6: return launch(k_forward<WT, 2, LPP, 6, SPAN, LC>); \
-                case 7: return launch(k_forward<WT, 2, LPP, 7, SPAN, LC>); \
-                case 8: return launch(k_forward<WT, 2, LPP, 8, SPAN, LC>); \
-                case 9: return launch(k_forward<WT, 2, LPP, 9, SPAN, LC>); \
+                case 2: return launch(k_forward<WT, 2, LPP, 2, SPAN>); \
+                case 3: return launch(k_forward<WT, 2, LPP, 3, SPAN>); \
+                case 4: return launch(k_forward<WT, 2, LPP, 4, SPAN>); \
+                case 5: return launch(k_forward<WT, 2, LPP, 5, SPAN>); \
+                case 6: return launch(k_forward<WT, 2, LPP, 6, SPAN>); \
+                case 7: return launch(k_forward<WT, 2, LPP, 7, SPAN>); \
+                case 8: return launch(k_forward<WT, 2, LPP, 8, SPAN>); \
+                case 9: return launch(k_forward<WT, 2, LPP, 9, SPAN>); \
                 default: return SD_EINVAL;                               \
             }                                                            \
     }
 #define SDFP_LAUNCH_HD(LPP)                                              \
-    if (role == 0) return launch(k_forward<WT, 0, LPP, 0, false, true>);                 \
-    if (long_ctx) {                                                                      \
-        if (c->span) { SDFP_LAUNCH_ROWS(LPP, true, true) } else { SDFP_LAUNCH_ROWS(LPP, false, true) }   \
-    } else {                                                                             \
-        if (c->span) { SDFP_LAUNCH_ROWS(LPP, true, false) } else { SDFP_LAUNCH_ROWS(LPP, false, false) } \
-    }
+    if (role == 0) return launch(k_forward<WT, 0, LPP, 0, false>);        \
+    if (c->span) { SDFP_LAUNCH_ROWS(LPP, true) } else { SDFP_LAUNCH_ROWS(LPP, false) }
     switch (g.head_dim) {   // config_ok admits 16, 32, 64, 128
         case 16: SDFP_LAUNCH_HD(4)
         case 32: SDFP_LAUNCH_HD(8)
@@ -640,8 +630,6 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
     float* rs = reinterpret_cast<float*>(base + pl.rs);
     bf16_t* xs_a = reinterpret_cast<bf16_t*>(base + pl.xs_a);
     bf16_t* xs_b = reinterpret_cast<bf16_t*>(base + pl.xs_b);
-    unsigned* counters = reinterpret_cast<unsigned*>(base + pl.counters);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(256), 0, c->stream, counters, PANEL_MAX_AWG);
     const LayerDims L{g.d_model, g.n_heads, g.n_kv_heads, g.head_dim, g.d_ffn, g.vocab, g.max_seq};
     int e;
     float* shares = reinterpret_cast<float*>(base + pl.shares);
@@ -737,7 +725,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             std::memset(&t, 0, sizeof(t));
             t.q = q; t.att = att; t.kc = kc; t.vc = vc;
             t.part = reinterpret_cast<float*>(base + pl.part); t.part_stride = pl.part_stride; t.part_ml_off = pl.part_ml_off;
-            t.counters = counters; t.M = np; t.pos0 = p0; t.L = L;
+            t.M = np; t.pos0 = p0; t.L = L;
             const int n_chunks = (np + MAX_ROWS - 1) / MAX_ROWS, grp = g.n_heads / g.n_kv_heads;
             const int n_act = (p0 + np + ATT_SL - 1) / ATT_SL;
             // Attention on the matrix cores (head_dim 64 and 128) or on the vector ALUs: whichever the times of
@@ -833,10 +821,8 @@ int do_prefill(sd_ctx* c, const int32_t* prompt_host, int n, int mode, const flo
     if (e) return e;
     HIPCHK(c, hipMemcpyAsync(c->prompt(), prompt_host, sizeof(int) * (size_t)n, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));   // prompt_host may be reused by the caller on return
-    // a fresh sequence starts from clean barrier and split-merge counters (also the way out of SD_ETIMEOUT)
+    // a fresh sequence starts from clean barrier counters (also the way out of SD_ETIMEOUT)
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.bar), BAR_WORDS + 1);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<unsigned*>(c->ws + c->cv.counters),
-                       c->cfg.n_kv_heads);
     const bool keep = mode == SD_SAMPLE || c->keep_logits;
     const bool gemm = std::is_same<WT, bf16_t>::value && c->panel.P > 0 && pf_panels_hold(c->cfg.head_dim, n) &&
                       (c->prefill_mode == 1 || (c->prefill_mode < 0 && n >= PREFILL_MATRIX_MIN_ROWS));

@@ -8,17 +8,16 @@ namespace sdfp {
 // A workgroup handles one split of ATT_SL positions of one KV head for all rows
 // and all query heads of the group -- or, where splits x KV heads leave most of the grid idle (grouped-query models:
 // 8 KV heads x 9 splits for 48 query vectors each), for one of n_qparts shares of those query vectors; a query's
-// arithmetic does not depend on which others share its workgroup, and the KV head's merge counter then expects
-// n_qparts arrivals per split.  K and V rows are read once, straight from the cache with coalesced
-// row loads (lanes split head_dim), scores are reduced on the DPP network, soft-max statistics per split go
-// to the workspace, and the last workgroup of a KV head to finish merges the splits in ascending order.
+// arithmetic does not depend on which others share its workgroup.  K and V rows are read once, straight from the cache with coalesced
+// row loads (lanes split head_dim), scores are reduced on the DPP network, outputs and soft-max statistics per split go
+// to the workspace, and the splits are merged in ascending order: by attn_merge, dealt over the grid, in the forward
+// kernels, by the workgroup's own last call in the prompt path's kernel.
 struct AttnArgs {
     const float* q;    // [M][H*hd]
     float* att;        // [M][H*hd]
     float* part_o;     // [n_splits][MAX_ROWS][part_H][hd]: partials of query heads part_h0 .. part_h0 + part_H - 1
     float* part_ml;    // [n_splits][MAX_ROWS][part_H][2]
     int part_H, part_h0;   // the forward kernel keeps all heads (H, 0); the prompt path one KV head's group per region
-    unsigned* counters;  // merge counters, left at 0: of KV head g at counters[g] (forward kernels), or the caller's own (panel)
     LayerDims L;
     Rows rows;
     const DevState* st;
@@ -67,20 +66,16 @@ template <> struct Row4<float> {
 // PANEL (prompt path): one workgroup runs the splits of a (16-row chunk, KV head) one after another, split 0 first, into
 // partial buffers of its own that hold one KV head's group.  Same arithmetic, operation for operation; what differs
 // is how the work lies on the lanes and what surrounds it: the scores are computed with a key per lane and the queries
-// in scalar registers (below; no cross-lane steps, no staging of the queries), the last call merges (no counter: every
+// in scalar registers (below; no cross-lane steps, no staging of the queries), the last call merges (every
 // partial is the workgroup's own, one wait for the stores in front of the merge), and values are widened once instead
 // of once per query (there are registers for it here).  (Skipping the row loads whose positions all lie beyond the
-// chunk's last row was tried: the branches cost more than the work they save.)  false (forward kernels): all heads,
-// one counter per KV head; these kernels have no register to spare for any of that.
-// LONGCTX: the context can hold more than 8 splits (max_seq > 8 * ATT_SL): more than 8 splits are merged by merge_long
-// (statistics staged in LDS, partials in batches).  The forward kernels of contexts that cannot hold as many keep the
-// compact one-split-at-a-time loop for that case instead (never run there): they sit at the register limit, and
-// merge_long's scalar registers alone cost their forwards 1 %.
+// chunk's last row was tried: the branches cost more than the work they save.)  false (forward kernels): all heads;
+// these kernels have no register to spare for any of that.
+// LONGCTX (PANEL): the panel ends beyond 8 splits: merge_long (statistics staged in LDS, partials in batches).
 template <typename WT, int LPP, int MROWS, bool PANEL = false, bool LONGCTX = true>
 __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* __restrict__ vc, const AttnArgs& a,
                                            float* lds, int split, int g, int qpart = 0, int n_qparts = 1) {
     const int part_H = PANEL ? a.part_H : a.L.H, part_h0 = PANEL ? a.part_h0 : 0;
-    unsigned* const counter = PANEL ? a.counters : a.counters + g;
     constexpr int QC = PANEL ? ATT_QC_PANEL : ATT_QC;   // query vectors per pass
     constexpr int PPL = 64 / LPP;            // positions covered by one wave-wide row load
     constexpr int NL = ATT_PPW / PPL > 0 ? ATT_PPW / PPL : 1;   // row loads per wave per split
@@ -262,20 +257,11 @@ __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* 
         }
         __syncthreads();
     }
-    if (direct) return;
-    // last workgroup of this KV head merges the splits
-    if constexpr (PANEL) {
-        if (split != n_active - 1) return;   // uniform; the partials are this workgroup's own, the last call merges
-        stores_done();
-        __syncthreads();
-    } else {
-        stores_done();
-        __syncthreads();
-        __shared__ unsigned s_last;
-        if (tid == 0) s_last = (atomic_inc_g(counter) == (unsigned)(n_active * n_qparts - 1)) ? 1u : 0u;
-        __syncthreads();
-        if (!s_last) return;
-    }
+    if constexpr (!PANEL) return;   // attn_merge does the rest
+    // PANEL: the partials are this workgroup's own, the last call merges
+    if (split != n_active - 1) return;   // uniform
+    stores_done();
+    __syncthreads();
     // One output: the splits' partials weighted by exp(max_s - max) in ascending split order.
     auto merge = [&](int idx) {
         const int qi = idx / hd, dim = idx - qi * hd, m = qi / grp, hq = g * grp + (qi - m * grp);
@@ -320,9 +306,7 @@ __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* 
     };
     // More splits (contexts beyond 1024 positions): the same operations per output in the same order.  The statistics
     // of a chunk of query vectors go to LDS first (the scores and output partials there are dead by now; one round
-    // trip for all of them), so that an output's only loads are its partials, MB splits in flight at a time.  (One
-    // split at a time, statistics included, is a chain of some 70 memory round trips per output at 33 splits: 120 us
-    // per layer of a five-row forward with 20 query vectors per KV head at 4096 positions, most of that layer's time.)
+    // trip for all of them), so that an output's only loads are its partials, MB splits in flight at a time.
     auto merge_long = [&](int q_lo, int q_hi) {
         const int cap = QC * ATT_SL + NWAVE * QC * hd;                // floats of the scores and the output partials
         constexpr int MB = 8;
@@ -338,11 +322,9 @@ __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* 
                 stat[e * 2] = __uint_as_float(v.x); stat[e * 2 + 1] = __uint_as_float(v.y);
             }
             __syncthreads();
-            // A thread takes W consecutive outputs of a query vector: one partial load per split, the weights once.  One
-            // row: W = 1, which covers the group's query vectors with an output per thread (the one-row kernels have no
-            // registers for more: 16-byte partials put three of theirs into scratch memory and cost 4 us per layer).
-            constexpr int W = MROWS == 1 ? 1 : 4;
-            const int per_q = W == 4 ? LPP : hd;
+            // a thread takes 4 consecutive outputs of a query vector: one partial load per split, the weights once
+            constexpr int W = 4;
+            const int per_q = LPP;
             for (int u = tid; u < nqc * per_q; u += WG_THREADS) {
                 const int ql = u / per_q, d0 = (u - ql * per_q) * W, qi = qc0 + ql;
                 const int m = qi / grp, hq = g * grp + (qi - m * grp), hp = hq - part_h0;
@@ -362,12 +344,8 @@ __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* 
                         for (int e = 0; e < W; ++e) os[sp][e] = 0.f;
                         if (s0 + sp < n_active) {
                             const float* src = o0 + (size_t)(s0 + sp) * o_split;
-                            if constexpr (W == 4) {
-                                const f32x4 v = ld_coh4(src);
-                                os[sp][0] = v.x; os[sp][1] = v.y; os[sp][2] = v.z; os[sp][3] = v.w;
-                            } else {
-                                os[sp][0] = ld_coh(src);
-                            }
+                            const f32x4 v = ld_coh4(src);
+                            os[sp][0] = v.x; os[sp][1] = v.y; os[sp][2] = v.z; os[sp][3] = v.w;
                         }
                     }
 #pragma unroll
@@ -382,31 +360,105 @@ __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* 
                     }
                 }
                 float* dst = a.att + (size_t)m * H * hd + (size_t)hq * hd + d0;
-                if constexpr (W == 4) st_coh4(dst, f32x4{num[0] / den, num[1] / den, num[2] / den, num[3] / den});
-                else st_coh(dst, num[0] / den);
+                st_coh4(dst, f32x4{num[0] / den, num[1] / den, num[2] / den, num[3] / den});
             }
         }
     };
-    auto merge_queries = [&](int q_lo, int q_hi) {   // query vectors [q_lo, q_hi) of the group
-        if (LONGCTX && n_active > 8) {
-            merge_long(q_lo, q_hi);
-        } else {
-            for (int idx = q_lo * hd + tid; idx < q_hi * hd; idx += WG_THREADS) merge(idx);
-        }
-    };
-    if (MROWS >= 2) {
-        // The rows go to the next phase without a grid barrier, and its readers poll row 0 only: rows 1.. first,
-        // their acknowledgement by every wave, row 0 last.  Row 0 is the first grp query vectors.
-        merge_queries(grp, nq);
-        stores_done();
-        __syncthreads();
-        merge_queries(0, grp);
+    if (LONGCTX && n_active > 8) {
+        merge_long(0, nq);
     } else {
-        merge_queries(0, nq);
+        for (int idx = tid; idx < nq * hd; idx += WG_THREADS) merge(idx);
     }
-    if constexpr (!PANEL) {
-        stores_done();
-        if (tid == 0) st_coh(counter, 0u);   // re-arm (coherent: the next arrivals come from other XCDs)
+}
+
+// The merge of the forward kernels: outputs [d0, d0 + D) of one query head for all rows, the splits' partials weighted by
+// exp(max_s - max) in ascending split order.  It is dealt over the whole grid (unit = head x 32 columns), whoever computed
+// the partials, and waits for them by polling: they are armed like the hand-over buffers (before the first attention of a
+// launch, and again by the workgroup that writes them; see Forward::arm_partials), so their way is one store and one poll
+// and not store, acknowledgement, counter, load.  The last workgroup of a KV head to finish used to merge it alone: with 20
+// query vectors at 33 splits that took 16 us of a layer's 44 us of attention (five rows of the Llama-3-8B shape at 4000
+// positions: 5.16 -> 4.56 ms a forward; 13B shape at 1024, seven rows: 9 %).  Every workgroup polls only after all its own
+// partials are stored, so no wait is for a workgroup that waits.
+constexpr int ATT_MERGE_D = 32;                                  // a 128-byte line: readers poll whole lines of row 0
+constexpr int ATT_MERGE_U = 4;                                   // 16-byte loads in flight per thread
+constexpr int ATT_MERGE_BUF = ATT_MERGE_U * 4 * WG_THREADS;      // floats
+template <int MROWS>
+__device__ __forceinline__ void attn_merge(const AttnArgs& a, float* lds, int lds_floats, int unit, int n_active, unsigned* bar,
+                                           unsigned spin_limit) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // keeps what depends on it from being hoisted out of the phase loop, into registers
+    const int hd = a.L.hd, H = a.L.H, M = MROWS > 0 ? MROWS : a.rows.M;
+    const int D = min(hd, ATT_MERGE_D), n_sl = hd / D, D4 = D >> 2, hq = unit / n_sl, d0 = (unit - hq * n_sl) * D;
+    float* buf = lds;                        // [split of the chunk][row][D]
+    float* stat = lds + ATT_MERGE_BUF;       // [row][n_active][max, sum]
+    // rows at a time: all of them unless their statistics do not fit (beyond 124000 positions with 16 rows); row 0 comes last
+    const int rb = min(M, max(1, (lds_floats - ATT_MERGE_BUF) / (2 * n_active)));
+    for (int m_hi = M; m_hi > 0; m_hi -= rb) {
+        const int m_lo = max(0, m_hi - rb), R = m_hi - m_lo;
+        // statistics: a thread's first pair travels with the first partials below
+        const int n_stat = R * n_active;
+        auto stat_at = [&](int e) {
+            const int r = e / n_active, sp = e - r * n_active;
+            return a.part_ml + (((size_t)sp * MAX_ROWS + m_lo + r) * H + hq) * 2;
+        };
+        auto unset = [](const u32x2& v) { return v.x == HANDOVER_ARMED || v.y == HANDOVER_ARMED; };
+        for (int e = tid + WG_THREADS; e < n_stat; e += WG_THREADS) {
+            u32x2 v = ld_coh8(stat_at(e));
+            for (unsigned spins = 0; unset(v) && poll_again(bar, spin_limit, spins);) v = ld_coh8(stat_at(e));
+            stat[e * 2] = __uint_as_float(v.x); stat[e * 2 + 1] = __uint_as_float(v.y);
+        }
+        // a thread's loads: column quad t % D4 of row (t / D4) % R, every spp-th split from t / (R * D4) on -- one offset per
+        // thread, the rest of the addresses is wave-uniform (the one-row kernels have hardly a register left)
+        const int per = R * D4, spp = WG_THREADS / per, sp_t = tid / per, rem = tid - sp_t * per, r_l = rem / D4;
+        const unsigned off = (unsigned)(((sp_t * MAX_ROWS + m_lo + r_l) * H + hq) * hd + d0 + (rem - r_l * D4) * 4);
+        const size_t split_floats = (size_t)MAX_ROWS * H * hd;
+        const int r_t = tid / D, dd = tid - r_t * D;
+        float num = 0.f, den = 0.f, gmax = -INFINITY;
+        for (int s0 = 0; s0 < n_active; s0 += ATT_MERGE_U * spp) {
+            const int n = min(ATT_MERGE_U * spp, n_active - s0), n_t = sp_t < spp ? n - sp_t : 0;   // valid: u * spp < n_t
+            f32x4 x[ATT_MERGE_U];
+            u32x2 st{0u, 0u};
+            const bool with_stat = s0 == 0 && tid < n_stat;
+            for (unsigned spins = 0;;) {
+                if (with_stat) st = ld_coh8(stat_at(tid));
+                bool armed = false;
+#pragma unroll
+                for (int u = 0; u < ATT_MERGE_U; ++u)
+                    if (u * spp < n_t) x[u] = ld_coh4(a.part_o + (size_t)(s0 + u * spp) * split_floats + off);
+#pragma unroll
+                for (int u = 0; u < ATT_MERGE_U; ++u) armed = armed || (u * spp < n_t && armed4(x[u]));
+                armed = armed || unset(st);
+                if (!__any(armed) || !poll_again(bar, spin_limit, spins)) break;
+            }
+#pragma unroll
+            for (int u = 0; u < ATT_MERGE_U; ++u)
+                if (u * spp < n_t) *reinterpret_cast<f32x4*>(buf + (u * spp * per + tid) * 4) = x[u];
+            if (with_stat) { stat[tid * 2] = __uint_as_float(st.x); stat[tid * 2 + 1] = __uint_as_float(st.y); }
+            __syncthreads();
+            if (tid < R * D) {
+                const float* sq = stat + (size_t)r_t * n_active * 2;
+                if (s0 == 0)
+                    for (int sp = 0; sp < n_active; ++sp) gmax = fmaxf(gmax, sq[sp * 2]);
+                for (int sp = 0; sp < n; ++sp) {
+                    const float ms = sq[(s0 + sp) * 2], w = (ms > -INFINITY) ? __expf(ms - gmax) : 0.f;
+                    num = fmaf(w, buf[(sp * R + r_t) * D + dd], num);
+                    den = fmaf(w, sq[(s0 + sp) * 2 + 1], den);
+                }
+            }
+            __syncthreads();
+        }
+        // The rows go to the next phase by the data itself, and its readers poll row 0 only: rows 1.. first, their
+        // acknowledgement by every wave, row 0 last.
+        const bool mine = tid < R * D;
+        float* dst = a.att + (size_t)(m_lo + r_t) * H * hd + (size_t)hq * hd + d0 + dd;
+        if (mine && m_lo + r_t > 0) st_coh(dst, num / den);
+        if (m_lo == 0) {
+            if (MROWS != 1) {
+                stores_done();
+                __syncthreads();
+            }
+            if (mine && r_t == 0) st_coh(dst, num / den);
+        }
     }
 }
 

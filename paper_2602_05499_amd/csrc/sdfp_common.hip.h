@@ -228,10 +228,30 @@ constexpr int BAR_FLAG_OFF = BAR_STRIDE;
 // only a NaN with this very payload in the caller's weights could imitate it, and then the bounded wait ends the
 // forward with the time-out flag instead of a result.
 constexpr unsigned HANDOVER_ARMED = 0xFFFFFFFFu;
+__device__ __forceinline__ bool armed4(const f32x4& a) {
+    return max(max(__float_as_uint(a.x), __float_as_uint(a.y)), max(__float_as_uint(a.z), __float_as_uint(a.w))) == HANDOVER_ARMED;
+}
+__device__ __forceinline__ f32x4 armed_quad() {
+    const float a = __uint_as_float(HANDOVER_ARMED);
+    return f32x4{a, a, a, a};
+}
 __device__ __forceinline__ bool armed8(const f32x4& a, const f32x4& b) {   // any of the 8 values not written yet
     const unsigned m0 = max(max(__float_as_uint(a.x), __float_as_uint(a.y)), max(__float_as_uint(a.z), __float_as_uint(a.w)));
     const unsigned m1 = max(max(__float_as_uint(b.x), __float_as_uint(b.y)), max(__float_as_uint(b.z), __float_as_uint(b.w)));
     return max(m0, m1) == HANDOVER_ARMED;
+}
+
+// One more poll of a hand-over wait?  Wave-uniform.  The wait is bounded like the grid barrier's: past spin_limit polls the
+// sticky flag is raised, and a raised flag (by anyone) ends every later wait at once.
+__device__ __forceinline__ bool poll_again(unsigned* bar, unsigned spin_limit, unsigned& spins) {
+    ++spins;
+    if (spins > spin_limit) {
+        st_coh(bar + BAR_FLAG_OFF, 1u);   // every active lane stores the same word
+        return false;
+    }
+    if ((spins & 63u) == 1u && ld_coh(reinterpret_cast<const int*>(bar + BAR_FLAG_OFF)) != 0) return false;
+    __builtin_amdgcn_s_sleep(2);
+    return true;
 }
 
 // Wait until every store this wave has issued is acknowledged.  A wave calls this before the workgroup

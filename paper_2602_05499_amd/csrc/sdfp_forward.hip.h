@@ -29,7 +29,6 @@ struct FwdArgs {
     const void* tok_emb;
     const float *cosT, *sinT;
     float *part_o, *part_ml;
-    unsigned* att_counters;
     HeadOut head;
     int head_run, head_row_from;
     int kind_units[8], kind_Kd[8]; // distribution units and reduction length of every projection kind (equal in all layers)
@@ -66,7 +65,7 @@ __device__ __forceinline__ void bar_wait(unsigned* bar, unsigned epoch, int n_wg
     }
 }
 
-template <typename WT, int ROLE, int LPP, int MROWS, bool SPAN, bool LONGCTX>
+template <typename WT, int ROLE, int LPP, int MROWS, bool SPAN>
 struct Forward {
     static constexpr int ROWS = MROWS;   // rows of the launch when known at compile time, else 0 (see Projection)
     static_assert((ROLE == 0 && MROWS == 0) || ((ROLE == 1 || ROLE == 3) && MROWS == 1) || (ROLE == 2 && MROWS >= 2),
@@ -79,8 +78,8 @@ struct Forward {
     // of the launch, until every value is written (writers store row 0 last; see Projection).  That takes the
     // store acknowledgement, the counter round trips of the barrier and the skew between workgroups out of the
     // chain between a phase's last store and the next phase's first matrix-core step.  What still needs a grid barrier: embedding -> first phase (the arming must
-    // be complete before anybody polls), QKV -> attention (new cache rows are not armed; the split-merge
-    // counters and partial buffers are reused layer after layer) and the end of the launch.  Every activation
+    // be complete before anybody polls), QKV -> attention (new cache rows are not armed; the attention partials
+    // are, and that again in every layer, in front of this barrier) and the end of the launch.  Every activation
     // buffer of a launch is written once, so no reader can be overtaken by a later writer.
     static constexpr bool POLL = ROLE != 0;
     // The service wave's loader stops at every phase end where the wave has to wait for stores: everywhere with
@@ -92,6 +91,7 @@ struct Forward {
     int wg, n_wg, wave, M, pos0, n_trace;
     bool wt_on = false;   // wave timeline build: inside the traced window of phases
     unsigned epoch;
+    const float* att_prev = nullptr;   // the attention output of the previous layer of this launch
 
     __device__ __forceinline__ Forward(const FwdArgs& a, char* l) : A(a), lds(l) {}
 
@@ -164,24 +164,67 @@ struct Forward {
         }
     }
 
+    // How the attention of a forward is dealt: items = splits x KV heads, each to n_qparts workgroups.
+    // Fewer items than half the grid (grouped-query models at moderate contexts): the query vectors of an item are
+    // dealt to several workgroups.  (Doing the same for the few items beyond whole rounds of the grid -- 264 items on
+    // 256 workgroups -- measured the same per step: what the five-row forward gained, the one-row forwards lost.)
+    __device__ __forceinline__ int n_splits() const { return (pos0 + M + ATT_SL - 1) / ATT_SL; }
+    __device__ __forceinline__ int n_qparts(int n_items) const {
+        return 2 * n_items <= n_wg ? min(M * (A.L.H / A.L.Hkv), n_wg / n_items) : 1;
+    }
+    // one row of a context of one split: attn_split finishes its outputs, no partials
+    __device__ __forceinline__ bool unsplit(int n_active) const { return MROWS == 1 && n_active == 1; }
+
     __device__ __forceinline__ void attention(const Phase& p) {
         AttnArgs aa;
-        aa.q = p.xin; aa.att = p.out; aa.part_o = A.part_o; aa.part_ml = A.part_ml; aa.counters = A.att_counters;
+        aa.q = p.xin; aa.att = p.out; aa.part_o = A.part_o; aa.part_ml = A.part_ml;
         aa.part_H = A.L.H; aa.part_h0 = 0;
         aa.L = A.L; aa.rows = A.rows; aa.st = A.st;
-        const int n_active = (pos0 + M + ATT_SL - 1) / ATT_SL;
-        const int n_items = n_active * A.L.Hkv;
-        // Fewer items than half the grid (grouped-query models at moderate contexts): the query vectors of an item are
-        // dealt to several workgroups.  (Doing the same for the few items beyond whole rounds of the grid -- 264 items on
-        // 256 workgroups -- measured the same per step: what the five-row forward gained, the one-row forwards lost.)
-        const int nq = M * (A.L.H / A.L.Hkv);
-        const int n_qparts = 2 * n_items <= n_wg ? min(nq, n_wg / n_items) : 1;
-        for (int u = wg; u < n_items * n_qparts; u += n_wg) {
-            const int it = u / n_qparts, qpart = u - it * n_qparts;
+        const int n_active = n_splits(), n_items = n_active * A.L.Hkv, nqp = n_qparts(n_items);
+        for (int u = wg; u < n_items * nqp; u += n_wg) {
+            const int it = u / nqp, qpart = u - it * nqp;
             const int g = it / n_active, split = it - g * n_active;
-            attn_split<WT, LPP, ROWS, false, LONGCTX>((const WT*)p.kc, (const WT*)p.vc, aa, reinterpret_cast<float*>(lds), split, g,
-                                                      qpart, n_qparts);
+            attn_split<WT, LPP, ROWS>((const WT*)p.kc, (const WT*)p.vc, aa, reinterpret_cast<float*>(lds), split, g, qpart, nqp);
             __syncthreads();
+        }
+        att_prev = p.out;
+        if (unsplit(n_active)) return;
+        // units from the last workgroup on: the first ones have the items
+        const int n_units = A.L.H * (A.L.hd / min(A.L.hd, ATT_MERGE_D));
+        for (int u = n_wg - 1 - wg; u < n_units; u += n_wg) {
+            attn_merge<ROWS>(aa, reinterpret_cast<float*>(lds), LDS_ZERO_OFF / 4, u, n_active, A.bar, A.spin_limit);
+            __syncthreads();
+        }
+    }
+
+    // The service wave marks the partials that this workgroup will write as not written yet: at the start of the launch
+    // (the grid barrier after the embedding follows), and in every later QKV phase (the barrier in front of attention
+    // follows).  Then the previous layer's merges must have read them.  In the forwards without grid barriers that is
+    // seen from the outputs they made of them -- row 0 of this item's heads, stored last --, as a rule at once: the rows have
+    // come through the other projections since, unless this workgroup had no part in any of those.
+    __device__ __forceinline__ void arm_partials() const {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));   // keeps what depends on it from being hoisted out of the phase loop, into registers
+        const int H = A.L.H, hd = A.L.hd, grp = H / A.L.Hkv;
+        const int n_active = n_splits(), n_items = n_active * A.L.Hkv, nqp = n_qparts(n_items), nq = M * grp;
+        if (unsplit(n_active)) return;
+        for (int u = wg; u < n_items * nqp; u += n_wg) {
+            const int it = u / nqp, qpart = u - it * nqp;
+            const int g = it / n_active, split = it - g * n_active;
+            if (POLL && att_prev != nullptr)
+                for (int i = lane * 4; i < grp * hd; i += 256) {
+                    unsigned spins = 0;
+                    while (armed4(ld_coh4(att_prev + (size_t)g * grp * hd + i)) && poll_again(A.bar, A.spin_limit, spins)) {}
+                }
+            const int q_from = (nq * qpart) / nqp, q_to = (nq * (qpart + 1)) / nqp;
+            for (int e = lane * 4; e < (q_to - q_from) * hd; e += 256) {
+                const int ql = e / hd, qi = q_from + ql, m = qi / grp, hq = g * grp + (qi - m * grp);
+                const size_t at = ((size_t)split * MAX_ROWS + m) * H + hq;
+                st_coh4(A.part_o + at * hd + (e - ql * hd), armed_quad());
+                if (e == ql * hd) {
+                    st_coh(A.part_ml + at * 2, __uint_as_float(HANDOVER_ARMED)); st_coh(A.part_ml + at * 2 + 1, __uint_as_float(HANDOVER_ARMED));
+                }
+            }
         }
     }
 
@@ -209,7 +252,10 @@ struct Forward {
         // of a launch to the first projection, 7B shape).
         const Phase p0 = load_phase(A.prog, 0);
         const bool has_embed = p0.kind == PK_EMBED;
-        if (has_embed) embed(p0);   // (the list that holds the output head alone has none)
+        if (has_embed) {   // (the list that holds the output head alone has none)
+            embed(p0);
+            if (wave == SERVICE_WAVE) arm_partials();
+        }
         {   // The descriptor of every phase is read with scalar loads that start out cold, in the chain between two projections:
             // the workgroups of an XCD (id % 8) bring the list's cache lines into its L2 now, a few each.
             const int n_line = (A.n_prog * (int)sizeof(Phase) + 127) >> 7, per_xcd = (n_wg + 7) >> 3;
@@ -276,17 +322,17 @@ struct Forward {
                     st_coh(A.head.part_val + (size_t)wg * MAX_ROWS + (threadIdx.x & 63), -INFINITY);
                     st_coh(A.head.part_idx + (size_t)wg * MAX_ROWS + (threadIdx.x & 63), 0x7FFFFFFF);
                 }
+                if (p.kind == PK_QKV && att_prev != nullptr && wave == SERVICE_WAVE) arm_partials();
                 pj.run(ring, ld, ph);
             }
             SDFP_BEACON(100000 + ph * 10 + p.kind);
             const int nk = as_const(A.prog)[ph + 1].kind;
             if (nk == PK_END || (nk == PK_HEAD && !A.head_run)) break;
             if (POLL && p.kind != PK_EMBED && is_projection(nk)) {
-                // hand-over by data: only this workgroup's own waves meet (the epilogue has read its LDS inputs).
-                // After attention every wave first waits for its own stores: the reset of a split-merge counter
-                // must have landed long before the next layer's grid barrier lets anybody count on it again.
+                // hand-over by data: only this workgroup's own waves meet (the epilogue has read its LDS inputs).  Nobody
+                // waits for stores: behind attention the rows' order is kept by attn_merge, and the partials are armed
+                // again only after the merges have been seen to have read them.
                 mark(p.kind * 2);
-                if (all_stored) stores_done();
                 __syncthreads();
                 mark(p.kind * 2 + 1);
             } else {
@@ -320,13 +366,11 @@ struct Forward {
 // allocation without spills matter here (measured: with all attention and staging variants in one kernel the
 // instance was 45 % larger, spilled 58 VGPRs to scratch and every forward was 4-8 % slower).  The ROLE also gives
 // each use its own symbol in a profile.  SPAN: ring turns may go on into the next tile (see Turn); a second set of
-// instances for the shapes whose weight rows do not fill whole turns (e.g. d = 5120: five blocks).  LONGCTX: contexts
-// of more than 8 attention splits (max_seq > 1024) are possible, the merge of many splits is compiled in (see
-// attn_split); a third doubling of the decode instances, chosen by the context's max_seq.
-template <typename WT, int ROLE, int LPP, int MROWS, bool SPAN, bool LONGCTX>
+// instances for the shapes whose weight rows do not fill whole turns (e.g. d = 5120: five blocks).
+template <typename WT, int ROLE, int LPP, int MROWS, bool SPAN>
 __global__ __launch_bounds__(WG_THREADS, 1) void k_forward(FwdArgs args) {
     extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    Forward<WT, ROLE, LPP, MROWS, SPAN, LONGCTX> f(args, lds_raw);
+    Forward<WT, ROLE, LPP, MROWS, SPAN> f(args, lds_raw);
     f.run();
 }
 

@@ -562,7 +562,6 @@ struct PfAttn {
     float* part;           // per workgroup: part_o [n_splits][16][grp][hd] then part_ml [n_splits][16][grp][2]
     size_t part_stride;    // floats per workgroup region
     size_t part_ml_off;    // floats from a region's start to its part_ml
-    unsigned* counters;    // one per workgroup, left at 0
     int M;                 // valid rows of the panel
     int pos0;              // absolute position of the panel's row 0
     LayerDims L;
@@ -577,7 +576,6 @@ __global__ __launch_bounds__(WG_THREADS, 4) void k_pf_attn(PfAttn a) {   // 4 wa
     AttnArgs aa;
     aa.part_o = a.part + (size_t)blockIdx.x * a.part_stride;
     aa.part_ml = aa.part_o + a.part_ml_off;
-    aa.counters = a.counters + blockIdx.x;
     aa.part_H = grp;
     aa.L = a.L; aa.st = nullptr;
     for (int it = blockIdx.x; it < n_chunks * a.L.Hkv; it += gridDim.x) {

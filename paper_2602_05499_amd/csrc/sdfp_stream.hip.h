@@ -525,18 +525,7 @@ struct Projection {
         if constexpr (COH) return ld_coh4(q);
         else return ld_act4(q);
     }
-    // One more poll of a hand-over wait?  Wave-uniform.  The wait is bounded like the grid barrier's: past
-    // spin_limit polls the sticky flag is raised, and a raised flag (by anyone) ends every later wait at once.
-    __device__ __forceinline__ bool poll_again(unsigned& spins) const {
-        ++spins;
-        if (spins > spin_limit) {
-            st_coh(bar + BAR_FLAG_OFF, 1u);   // every active lane stores the same word
-            return false;
-        }
-        if ((spins & 63u) == 1u && ld_coh(reinterpret_cast<const int*>(bar + BAR_FLAG_OFF)) != 0) return false;
-        __builtin_amdgcn_s_sleep(2);
-        return true;
-    }
+    __device__ __forceinline__ bool poll_again(unsigned& spins) const { return sdfp::poll_again(bar, spin_limit, spins); }
 
     // sub-phase timeline entry: tag = 32 + kind * 4 + {0: first activation block staged, 1: all items done,
     // 2: epilogue stores issued}
