@@ -676,8 +676,8 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
         const int jt = np <= 16 ? 1 : (np <= 32 ? 2 : 4);
 #define SDFP_PF_ONE_TILE(KIND, PART)                                                                               \
     (jt == 1 ? launch_pf(c, k_pf_gemm<KIND, 1, PART, 1>, gemm_grid(a), blk, PF_LDS_BYTES, a)                      \
-             : jt == 2 ? launch_pf(c, k_pf_gemm<KIND, 1, PART, 2>, gemm_grid(a), blk, PF_LDS_BYTES, a)            \
-                       : launch_pf(c, k_pf_gemm<KIND, 1, PART, 4>, gemm_grid(a), blk, PF_LDS_BYTES, a))
+             : jt == 2 ? launch_pf(c, k_pf_gemm<KIND, 2, PART, 2, 2>, gemm_grid(a), blk, PF_LDS_BYTES, a)            \
+                       : launch_pf(c, k_pf_gemm<KIND, 2, PART, 4, 2>, gemm_grid(a), blk, PF_LDS_BYTES, a))
         const int my = (np + PF_TM - 1) / PF_TM;
         const bool fused = d <= PF_FUSED_MAX_D;   // residual + row norm + split in one kernel (rows that fit its registers)
         hipLaunchKernelGGL(k_pf_embed, dim3(np), dim3(256), 0, c->stream, c->prompt() + p0,
@@ -708,7 +708,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             if (nt_qkv > 1) {
                 a.n_nt = (a.n_tiles + 8 * nt_qkv - 1) / (8 * nt_qkv);
                 e = nt_qkv == 3 ? launch_pf(c, k_pf_gemm<PF_QKV, 3, false>, gemm_grid(a), blk, PF_LDS_BYTES, a)
-                                : launch_pf(c, k_pf_gemm<PF_QKV, 2, false>, gemm_grid(a), blk, PF_LDS_BYTES, a);
+                                : launch_pf(c, k_pf_gemm<PF_QKV, 4, false, 4, 2>, gemm_grid(a), blk, PF_LDS_BYTES, a);
             } else if (dealt_fits(a.n_tiles * 16) && share_groups((a.n_tiles + 7) / 8, my) > 1) {
                 // short prompt: shares dealt to workgroups, then the epilogue
                 a.n_nt = (a.n_tiles + 7) / 8; a.n_groups = share_groups(a.n_nt, my);
@@ -779,7 +779,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             if (nt_gu > 1) {
                 a.n_nt = (a.n_tiles + 8 * nt_gu - 1) / (8 * nt_gu);
                 e = nt_gu == 3 ? launch_pf(c, k_pf_gemm<PF_GATEUP, 3, false>, gemm_grid(a), blk, PF_LDS_BYTES, a)
-                               : launch_pf(c, k_pf_gemm<PF_GATEUP, 2, false>, gemm_grid(a), blk, PF_LDS_BYTES, a);
+                               : launch_pf(c, k_pf_gemm<PF_GATEUP, 4, false, 4, 2>, gemm_grid(a), blk, PF_LDS_BYTES, a);
             } else {   // (dealing the shares as for QKV does not pay here: 172 workgroups as it is, 72 vs 65 us on the 7B shape)
                 a.n_nt = (a.n_tiles + 7) / 8;
                 e = SDFP_PF_ONE_TILE(PF_GATEUP, false);

@@ -93,16 +93,16 @@ size_t fit_tcache_offset(const FitDims& D, int l, int slot) {
 size_t fit_tcache_bytes(const FitDims& D) { return fit_tcache_offset(D, D.L, 0) + up256((size_t)D.V * D.d * 2); }
 
 // out = base + X W^T (base may be out, or nullptr for zero): X [T][K] float32, W [N][K] bfloat16, out and base [T][ldo]
-template <int NT, bool PARTIAL>
+template <int NT, bool PARTIAL, int WJ = 1>
 void fit_gemm_launch(const Fit& F, const PfGemm& a) {
     static bool attr_done = false;   // per kernel instance
     if (!attr_done) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_pf_gemm<PF_PLAIN, NT, PARTIAL>),
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_pf_gemm<PF_PLAIN, NT, PARTIAL, 4, WJ>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, PF_LDS_BYTES);
         attr_done = true;
     }
     const unsigned grid = (unsigned)((a.n_nt * a.n_groups + 7) / 8 * 8 * a.my);
-    hipLaunchKernelGGL((k_pf_gemm<PF_PLAIN, NT, PARTIAL>), dim3(grid), dim3(WG_THREADS), PF_LDS_BYTES, F.st, a);
+    hipLaunchKernelGGL((k_pf_gemm<PF_PLAIN, NT, PARTIAL, 4, WJ>), dim3(grid), dim3(WG_THREADS), PF_LDS_BYTES, F.st, a);
 }
 // A weight operand: the matrix and whether it lies in tile order (pf_tile_weights) or row-major
 struct FitW { const void* p; bool tiled; };
@@ -134,7 +134,7 @@ void fit_gemm(const Fit& F, FitW Wt, int N, int K, const float* X, const float* 
         hipLaunchKernelGGL(k_pf_residual, dim3(512), dim3(256), 0, F.st, base, out, F.f(F.cv.shares), a.part_arr, T * N / 4);
     } else {
         a.n_nt = (a.n_tiles + 7) / 8;
-        fit_gemm_launch<1, false>(F, a);
+        fit_gemm_launch<2, false, 2>(F, a);
     }
 }
 // W^T of W [R][C], in tile order, into the scratch matrix, or into (from the second sample on: out of) the call's cache

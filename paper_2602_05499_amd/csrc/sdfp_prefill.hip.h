@@ -39,7 +39,8 @@ constexpr int PF_BLOCK_BYTES = PF_NSHARE * PF_SPS * PF_STEP_BYTES;   // 2 KB
 constexpr int PF_TM = 64;                // prompt rows per workgroup tile
 constexpr int PF_FRAG_BYTES = 16 * PF_STEP_BYTES;          // one B operand: a step of 16 prompt rows, lane l's 16 bytes at l * 16
 constexpr int PF_SLAB_BYTES = 3 * (PF_TM / 16) * PF_SPS * PF_FRAG_BYTES;   // pieces x column tiles x steps: 48 KB
-constexpr int PF_LDS_BYTES = 2 * PF_SLAB_BYTES;            // double-buffered
+constexpr int PF_SLABS = 3;                                // slabs of LDS: one is multiplied, two are on their way
+constexpr int PF_LDS_BYTES = PF_SLABS * PF_SLAB_BYTES;
 
 // Byte offset, inside one piece of an input with rows of Kd values, of the 16-byte unit that holds values 8 * k8 .. + 7 of
 // row m: [16-row tile][64-byte step][quarter of the step][row of the tile][16 bytes].  A piece spans a whole number of
@@ -264,7 +265,8 @@ __global__ __launch_bounds__(256) void k_pf_tile_weights(PfGemm a, bf16_t* __res
 // partial sums P_p to part[p][row][N], and k_pf_residual (k_pf_finish_qkv) adds them in share order.
 // JT: 16-row column tiles of the workgroup tile that are multiplied (4; 1 or 2 for a panel of at most 16 or 32 rows,
 // which then costs a quarter or half of the matrix-core instructions and LDS reads, and fetches as much less).
-template <int KIND, int NT, bool PARTIAL, int JT = 4>
+constexpr int pf_weight_depth(int nt) { return nt == 1 ? 3 : (nt == 2 ? 2 : 1); }   // slabs of weights in a wave's registers
+template <int KIND, int NT, bool PARTIAL, int JT = 4, int WJ = 1>
 __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -274,7 +276,9 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
     if (col >= a.n_nt * a.n_groups) return;                 // uniform over the workgroup
     const int grp = col % a.n_groups;
     const int m0 = (place % a.my) * PF_TM;                  // first prompt row of the workgroup tile
-    const int t0 = (col / a.n_groups) * (8 * NT) + wave * NT;   // the wave's first weight tile
+    constexpr int JW = JT / WJ;                             // the wave's column tiles, j0 ..
+    const int j0 = (wave % WJ) * JW;
+    const int t0 = (col / a.n_groups) * (8 / WJ * NT) + wave / WJ * NT;   // the wave's first weight tile
     const int pitch = a.Kd * 2;                             // bytes per weight row
     const int S = pitch / PF_STEP_BYTES;                    // steps per weight row
     const int nblk = (S + PF_NSHARE * PF_SPS - 1) / (PF_NSHARE * PF_SPS);
@@ -307,11 +311,11 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
     const int spg = PF_NSHARE / a.n_groups;                 // shares per group
     const int i_lo = grp * spg * nblk, i_hi = i_lo + spg * nblk;
 
-    f32x4 total[PARTIAL ? 1 : NT][PARTIAL ? 1 : JT], acc[NT][JT];
+    f32x4 total[PARTIAL ? 1 : NT][PARTIAL ? 1 : JW], acc[NT][JW];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int j = 0; j < JT; ++j) {
+        for (int j = 0; j < JW; ++j) {
             acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (!PARTIAL) total[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -319,7 +323,9 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
     // Every load of the loop below is unconditional and its address clamped into the row: a load under a condition makes
     // the compiler wait, at the join, for everything in flight, and the pipeline (pieces and weights one slab ahead)
     // would stall once per step.  What a clamped load brings is never used: the steps a slab does not have are skipped.
-    u32x4 wa[NT][PF_SPS];   // the wave's weight steps: of this slab until a step is multiplied, of the next one after
+    // the wave's weight steps, WD slabs of them: a step's registers take the step WD slabs further on when it is multiplied
+    constexpr int WD = pf_weight_depth(NT);
+    u32x4 wa[WD][NT][PF_SPS];
     const int last_tile16 = (a.M - 1) >> 4;
     // Slab i into LDS buffer buf; wave w fetches fragments w, w + 8, ...  The loads are counted with the wave's other
     // vector memory loads and complete in order with them.  They are issued from an asm statement: told what they are,
@@ -344,26 +350,29 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
                          : "memory");   // (M0 is not allocatable: the compiler sets it in front of each of its own uses)
         }
     };
-    auto load_weight_step = [&](int byte0, int s) {
+    auto load_weight_step = [&](int byte0, int s, u32x4 (&w)[NT][PF_SPS]) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
-            wa[t][s] = *reinterpret_cast<const u32x4*>(wrow[t] + (size_t)(min((byte0 >> 6) + s, S - 1) * wstep));
+            w[t][s] = *reinterpret_cast<const u32x4*>(wrow[t] + (size_t)(min((byte0 >> 6) + s, S - 1) * wstep));
     };
-
+    const int i_last = i_hi - 1;                               // past the end the last slab is fetched again, unused
     fetch_slab(i_lo, 0);
 #pragma unroll
-    for (int s = 0; s < PF_SPS; ++s) load_weight_step(slab_byte0(i_lo), s);
+    for (int w = 0; w < WD; ++w)
+#pragma unroll
+        for (int s = 0; s < PF_SPS; ++s) load_weight_step(slab_byte0(min(i_lo + w, i_last)), s, wa[w]);
+    fetch_slab(min(i_lo + 1, i_last), 1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    for (int i = i_lo; i < i_hi; ++i) {
-        const int buf = (i - i_lo) & 1;
+    int buf = 0;                                               // LDS slab of slab i
+    auto slab = [&](int i, u32x4 (&w)[NT][PF_SPS]) {
         const int nst = slab_steps(i);
-        const int i_next = min(i + 1, i_hi - 1);               // the last slab fetches itself again, unused
-        const int byte0_next = slab_byte0(i_next);
-        // The next slab's pieces are fetched after this slab's first step (that buffer's last readers passed the barrier
-        // long ago): the loop's first instructions wait for registers that old loads may still target, and a fetch issued
-        // in front of them would be waited for as well, a memory round trip per slab.
-        const char* xb = lds + buf * PF_SLAB_BYTES + lane * 16;
+        const int byte0_next = slab_byte0(min(i + WD, i_last));
+        // The pieces of the slab after the next one, into the buffer whose last readers passed the barrier in front of this
+        // slab.  Two slabs ahead and in front of this slab's weight loads: memory answers in order, so the wait for the next
+        // slab's pieces at the end of this slab is for nothing younger than the previous slab's start.
+        fetch_slab(min(i + 2, i_last), buf == 0 ? 2 : buf - 1);
+        const char* xb = lds + buf * PF_SLAB_BYTES + j0 * (PF_SPS * PF_FRAG_BYTES) + lane * 16;
         auto frag = [&](int s, int j, int p) {
             return *reinterpret_cast<const u32x4*>(xb + ((p * 4 + j) * PF_SPS + s) * PF_FRAG_BYTES);
         };
@@ -374,7 +383,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
                     acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, wa[t][s]), __builtin_bit_cast(bf16x8, x3[p]), acc[t][j], 0, 0, 0);
+                        __builtin_bit_cast(bf16x8, w[t][s]), __builtin_bit_cast(bf16x8, x3[p]), acc[t][j], 0, 0, 0);
         };
         // Straight-line code for every slab: the B operands of a (step, column tile) are read from LDS while the previous
         // one is multiplied (read and used back to back, their latency showed in every group of instructions).  A step
@@ -387,14 +396,14 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
         for (int s = 0; s < PF_SPS; ++s) {
             if (s >= nst) {   // uniform; rare
 #pragma unroll
-                for (int t = 0; t < NT; ++t) wa[t][s] = u32x4{0u, 0u, 0u, 0u};
+                for (int t = 0; t < NT; ++t) w[t][s] = u32x4{0u, 0u, 0u, 0u};
             }
 #pragma unroll
-            for (int j = 0; j < JT; ++j) {
-                const int g = s * JT + j + 1;
-                if (g < JT * PF_SPS) {
+            for (int j = 0; j < JW; ++j) {
+                const int g = s * JW + j + 1;
+                if (g < JW * PF_SPS) {
 #pragma unroll
-                    for (int p = 0; p < 3; ++p) nxt[p] = frag(g / JT, g % JT, p);
+                    for (int p = 0; p < 3; ++p) nxt[p] = frag(g / JW, g % JW, p);
                 }
                 __builtin_amdgcn_sched_barrier(0);   // the reads stay in front of the instructions that hide them
                 multiply(s, j, cur);
@@ -402,17 +411,16 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
 #pragma unroll
                 for (int p = 0; p < 3; ++p) cur[p] = nxt[p];
             }
-            load_weight_step(byte0_next, s);              // this step's registers are free: the next slab's weights
-            if (s == 0) fetch_slab(i_next, buf ^ 1);
+            load_weight_step(byte0_next, s, w);           // this step's registers are free
         }
         if ((i + 1) % nblk == 0) {   // the share's partial sums are complete
             const int p = i / nblk;
 #pragma unroll
             for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int j = 0; j < JT; ++j) {
+                for (int j = 0; j < JW; ++j) {
                     if (PARTIAL) {
-                        const int tile = t0 + t, m = m0 + j * 16 + r16;
+                        const int tile = t0 + t, m = m0 + (j0 + j) * 16 + r16;
                         if (tile < a.n_tiles && m < a.M)
                             *reinterpret_cast<f32x4*>(a.part + (size_t)p * a.part_arr + (size_t)m * a.part_ld + tile * 16 + gq * 4) = acc[t][j];
                     } else {     // added in share order
@@ -423,10 +431,21 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
                     acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
         }
-        // the next slab has landed once at most the weight loads issued after it (three steps') are still on their way
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NT * (PF_SPS - 1)) : "memory");
+        // The next slab's pieces have landed once at most the loads issued after them are on their way: the previous slab's
+        // and this slab's weights, and this slab's pieces (of which a wave fetches at least MIN_FETCH).
+        constexpr int MIN_FETCH = JT == 4 ? 6 : (JT >= 2 ? 3 : 0);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NT * PF_SPS + MIN_FETCH) : "memory");
         __syncthreads();
+        buf = buf == PF_SLABS - 1 ? 0 : buf + 1;
+    };
+    int i = i_lo;
+    for (; i + WD <= i_hi; i += WD) {
+#pragma unroll
+        for (int w = 0; w < WD; ++w) slab(i + w, wa[w]);
     }
+#pragma unroll
+    for (int w = 0; w + 1 < WD; ++w)
+        if (i + w < i_hi) slab(i + w, wa[w]);
     if (PARTIAL) return;
 
     // ---- epilogue.  Lane l holds, per tile, prompt row (column) l % 16 and output rows 4 * (l / 16) .. + 3 of the tile.
@@ -435,8 +454,8 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
         const int tile = t0 + t;
         if (tile >= a.n_tiles) continue;
 #pragma unroll
-        for (int j = 0; j < JT; ++j) {
-            const int m = m0 + j * 16 + r16;
+        for (int j = 0; j < JW; ++j) {
+            const int m = m0 + (j0 + j) * 16 + r16;
             f32x4 v = total[PARTIAL ? 0 : t][PARTIAL ? 0 : j];
             if (KIND == PF_PLAIN) {
                 if (m < a.M) {
