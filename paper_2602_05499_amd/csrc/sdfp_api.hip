@@ -105,6 +105,7 @@ struct PanelPlan {
     size_t part_ml_off;    // floats from a region's start to its (max, sum) pairs
     int Ka;                // row length of xs_a: max(d_model, n_heads * head_dim)
 };
+static_assert(PF_TM == PF_ROWS && PF_NSHARE == PF_SHARES, "the plan's tile");
 constexpr int PANEL_MAX_ROWS = 512, PANEL_MAX_AWG = 512;   // (two attention workgroups per compute unit)
 constexpr size_t PANEL_MAX_BYTES = (size_t)1 << 30;   // a workspace never grows past this for the sake of a larger panel
 // bytes per panel row: residual stream, queries, attention output, reciprocal RMS, the pieces of the two projection
@@ -652,23 +653,9 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
     auto tiles_fill = [&](int n_tiles, int nt, int my, int groups) {
         return ((n_tiles + 8 * nt - 1) / (8 * nt)) * my * groups >= (c->n_cu * 3) / 8;
     };
-    // QKV and gate/up: 1, 2 or 3 tiles per wave -- whichever needs the least time by a simple model: rounds of workgroups
-    // on the compute units x tiles per wave x the relative cost of a tile at that size (smaller workgroup tiles read
-    // more LDS and L2 bytes per matrix-core instruction).  290 workgroups of 3 tiles are two rounds, 430 of 2 tiles two
-    // cheaper ones; 116 of 3 tiles fill half the chip, 172 of 2 tiles two thirds of it in two thirds of the time.
-    auto pick_nt = [&](int n_tiles, int my) {
-        const double w[4] = {0.0, 1.4, 1.1, 1.0};
-        int best = 3;
-        double best_cost = 1e30;
-        for (int nt = 3; nt >= 1; --nt) {
-            const int wgs = ((n_tiles + 8 * nt - 1) / (8 * nt)) * my;
-            const double cost = (double)((wgs + c->n_cu - 1) / c->n_cu) * nt * w[nt];
-            if (cost < best_cost - 1e-9) { best_cost = cost; best = nt; }
-        }
-        return best;
-    };
-    for (int p0 = 0; p0 < n; p0 += pl.P) {
-        const int np = std::min(pl.P, n - p0);
+    auto pick_nt = [&](int n_tiles, int my) { return pf_wide_tiles(n_tiles, my, c->n_cu); };
+    for (int p0 = 0, np = 0; p0 < n; p0 += np) {
+        np = std::min(n - p0, PF_TM * pf_next_panel(PfModel{d, hq, hkv, F, c->n_cu}, n - p0, pl.P / PF_TM));
         const dim3 blk(WG_THREADS);
         // the share sums of a projection of `outs` outputs fit the scratch that is sized for the panel's O / down sums
         auto dealt_fits = [&](int outs) { return (size_t)np * outs <= (size_t)pl.P * d; };
@@ -754,7 +741,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             a.xs = xs_a; a.xs_piece = pf_xs_piece(np, hq); a.Kd = hq; a.n_tiles = d / 16; a.rs = nullptr; a.h = h;
             a.wt = tiled_at(l, tl.o);
             if (tiles_fill(a.n_tiles, NT_NARROW, my, PF_NSHARE)) {
-                a.n_nt = (a.n_tiles + 8 * NT_NARROW - 1) / (8 * NT_NARROW); a.n_groups = share_groups(a.n_nt, my);
+                a.n_nt = (a.n_tiles + 8 * NT_NARROW - 1) / (8 * NT_NARROW); a.n_groups = pf_narrow_groups(a.n_nt * my, c->n_cu);
                 e = launch_pf(c, k_pf_gemm<PF_OPROJ, NT_NARROW, true>, gemm_grid(a), blk, PF_LDS_BYTES, a);
             } else {
                 a.n_nt = (a.n_tiles + 7) / 8; a.n_groups = share_groups(a.n_nt, my);
@@ -789,7 +776,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             a.xs = xs_b; a.xs_piece = pf_xs_piece(np, F); a.Kd = F; a.n_tiles = d / 16; a.rs = nullptr;
             a.wt = tiled_at(l, tl.down);
             if (tiles_fill(a.n_tiles, NT_NARROW, my, PF_NSHARE)) {
-                a.n_nt = (a.n_tiles + 8 * NT_NARROW - 1) / (8 * NT_NARROW); a.n_groups = share_groups(a.n_nt, my);
+                a.n_nt = (a.n_tiles + 8 * NT_NARROW - 1) / (8 * NT_NARROW); a.n_groups = pf_narrow_groups(a.n_nt * my, c->n_cu);
                 e = launch_pf(c, k_pf_gemm<PF_DOWN, NT_NARROW, true>, gemm_grid(a), blk, PF_LDS_BYTES, a);
             } else {
                 a.n_nt = (a.n_tiles + 7) / 8; a.n_groups = share_groups(a.n_nt, my);
@@ -801,7 +788,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
                 hipLaunchKernelGGL(k_pf_residual, dim3(512), dim3(256), 0, c->stream, h, h, shares, a.part_arr, np * d / 4);
         }
 #undef SDFP_PF_ONE_TILE
-        if (p0 + pl.P >= n)   // the prompt's last row goes to the output head
+        if (p0 + np >= n)   // the prompt's last row goes to the output head
             HIPCHK(c, hipMemcpyAsync(base + pl.h_last, h + (size_t)(np - 1) * d, (size_t)d * 4, hipMemcpyDeviceToDevice, c->stream));
     }
     HIPCHK(c, hipGetLastError());

@@ -249,12 +249,16 @@ __global__ __launch_bounds__(256) void k_pf_tile_weights(PfGemm a, bf16_t* __res
     }
 }
 
-// ---- the GEMM.  A workgroup computes 8 * NT weight tiles (128 * NT output rows) x PF_TM prompt rows; wave w owns the NT
-// weight tiles w * NT .. and all four 16-row column tiles, so a weight is read by one wave only and an input piece read
-// from LDS feeds NT matrix-core instructions.  Weights go from memory straight into the A operand (lane l: row l % 16,
-// bytes (l / 16) * 16 .. of the step, as in the decode kernels), one slab ahead; the input pieces of a slab -- the 4 steps
-// that one share owns in one block, for all 64 prompt rows -- are staged in LDS, double-buffered, and read as the B
-// operand (lane l: prompt row l % 16, the same bytes of the step).
+// ---- the GEMM.  A workgroup computes 8 / WJ * NT weight tiles x PF_TM prompt rows; WJ waves share NT weight tiles, each
+// with its part of the four 16-row column tiles, so that an input piece read from LDS feeds NT matrix-core instructions:
+// WJ = 1 with three or four tiles (a weight is read by one wave only), 2 where a workgroup has 8 or 16 tiles (with one or two
+// tiles per wave and all columns the LDS reads took as long as the matrix cores or longer).  Weights go from memory straight
+// into the A operand (lane l: row l % 16, bytes (l / 16) * 16 .. of the step, as in the decode kernels), WD slabs ahead; the
+// input pieces of a slab -- the 4 steps that one share owns in one block, for all 64 prompt rows -- are staged in LDS, two
+// slabs ahead in three buffers, and read as the B operand (lane l: prompt row l % 16, the same bytes of the step).
+// What bounds it: large tiles the matrix cores at the power limit (7B gate/up, 512 rows: 224 us, 1.24 PFLOP/s counting the
+// three passes; hipBLASLt's bf16 product of that size 286 us), 16 tiles 337 -> 318 us with this pipeline (Llama-3-8B gate/up),
+// 8 tiles the read of the weights (7B gate/up at 37 rows 65 -> 57 us, 3.2 TB/s).
 //
 // Workgroups that read the same weights (the panel's row tiles of one weight tile group) are neighbours on one XCD,
 // so the weights come from HBM once and from that XCD's L2 afterwards: workgroup id -> XCD id % 8, place id / 8 on it;
@@ -356,13 +360,16 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
             w[t][s] = *reinterpret_cast<const u32x4*>(wrow[t] + (size_t)(min((byte0 >> 6) + s, S - 1) * wstep));
     };
     const int i_last = i_hi - 1;                               // past the end the last slab is fetched again, unused
+    constexpr int MIN_FETCH = JT == 4 ? 6 : (JT >= 2 ? 3 : 0);   // pieces of a slab that every wave fetches at least
     fetch_slab(i_lo, 0);
 #pragma unroll
-    for (int w = 0; w < WD; ++w)
+    for (int s = 0; s < PF_SPS; ++s) load_weight_step(slab_byte0(i_lo), s, wa[0]);
+    fetch_slab(min(i_lo + 1, i_last), 1);
+#pragma unroll
+    for (int w = 1; w < WD; ++w)
 #pragma unroll
         for (int s = 0; s < PF_SPS; ++s) load_weight_step(slab_byte0(min(i_lo + w, i_last)), s, wa[w]);
-    fetch_slab(min(i_lo + 1, i_last), 1);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((WD - 1) * NT * PF_SPS + MIN_FETCH) : "memory");   // the first slab
     __syncthreads();
     int buf = 0;                                               // LDS slab of slab i
     auto slab = [&](int i, u32x4 (&w)[NT][PF_SPS]) {
@@ -431,10 +438,9 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
                     acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
         }
-        // The next slab's pieces have landed once at most the loads issued after them are on their way: the previous slab's
-        // and this slab's weights, and this slab's pieces (of which a wave fetches at least MIN_FETCH).
-        constexpr int MIN_FETCH = JT == 4 ? 6 : (JT >= 2 ? 3 : 0);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NT * PF_SPS + MIN_FETCH) : "memory");
+        // The next slab's pieces have landed once at most loads issued after them are on their way: this slab's pieces and
+        // weights and, with more than one slab of weights ahead, those of the slab before it (the prologue counts as one).
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((WD > 1 ? 2 : 1) * NT * PF_SPS + MIN_FETCH) : "memory");
         __syncthreads();
         buf = buf == PF_SLABS - 1 ? 0 : buf + 1;
     };

@@ -1,4 +1,4 @@
-// Which kernel runs the attention of a prompt panel (host arithmetic only).
+// The cut of a prompt into panels, the tiles of its GEMMs, and which kernel runs a panel's attention (host arithmetic only).
 #pragma once
 #include <algorithm>
 
@@ -85,6 +85,68 @@ inline bool pf_panels_hold(int hd, int n) { return hd >= 64 || (n + PF_SPLIT - 1
 inline bool pf_attn_on_matrix_cores(const PfAttnPanel& p) {
     if (p.wg_mx < 1) return false;
     return pf_chunk_splits(p, (p.M - 1) / PF_CHUNK) > PF_VALU_MAX_SPLITS || pf_mx_us(p) <= pf_valu_us(p);
+}
+
+
+// ---- tiles and panels of the GEMMs.  A launch takes whole rounds of workgroups on the compute units, one each; its time in
+// UNITS: one unit = a round of workgroups with one weight tile per wave over a reduction of 4096, 38 us.
+constexpr int PF_SHARES = 8, PF_ROWS = 64;   // shares of the reduction dimension, prompt rows per workgroup tile
+
+inline double pf_rounds(int wgs, int n_cu) { return (double)((wgs + n_cu - 1) / n_cu); }
+// QKV and gate/up with nt tiles per wave (and half the columns each at nt < 3): smaller tiles read more bytes per matrix-core
+// instruction (measured per tile at 512 rows: 37.6 us with three, 39.8 with two; at a reduction of 8192 the ratio is 1.14).
+inline double pf_wide_units(int n_tiles, int my, int nt, int n_cu) {
+    const double w[4] = {0.0, 1.4, 1.1, 1.0};
+    return pf_rounds((n_tiles + 8 * nt - 1) / (8 * nt) * my, n_cu) * nt * w[nt];
+}
+// 290 workgroups of 3 tiles are two rounds, 430 of 2 tiles two cheaper ones; 116 of 3 tiles fill half the chip, 172 of 2 tiles
+// two thirds of it in two thirds of the time.
+inline int pf_wide_tiles(int n_tiles, int my, int n_cu) {
+    int best = 3;
+    for (int nt = 2; nt >= 1; --nt)
+        if (pf_wide_units(n_tiles, my, nt, n_cu) < pf_wide_units(n_tiles, my, best, n_cu) - 1e-9) best = nt;
+    return best;
+}
+// O and down projection in tiles of 4 per wave: a tile's shares dealt to g workgroups, each with its prologue and its way out
+// (a fifth of a share of 4096).  80 workgroups (5120 outputs, 512 rows): 4 groups are 320 workgroups of two shares, two rounds
+// = 4.4 shares, 8 groups three rounds = 3.6.
+inline double pf_narrow_shares(int wgs, int g, int n_cu) { return pf_rounds(wgs * g, n_cu) * ((double)PF_SHARES / g + 0.2); }
+inline int pf_narrow_groups(int wgs, int n_cu) {
+    int best = 1;
+    for (int g = 2; g <= PF_SHARES; g *= 2)
+        if (pf_narrow_shares(wgs, g, n_cu) < pf_narrow_shares(wgs, best, n_cu) - 1e-9) best = g;
+    return best;
+}
+struct PfModel { int d, hq, hkv, F, n_cu; };
+// A layer's GEMMs over my row tiles, and half a unit for what a panel costs besides.
+inline double pf_panel_units(const PfModel& m, int my) {
+    const int qkv = (m.hq + 2 * m.hkv) / 16, gu = m.F / 8, out = (m.d + 511) / 512 * my;
+    const double narrow = pf_narrow_shares(out, pf_narrow_groups(out, m.n_cu), m.n_cu) * 4.0 / PF_SHARES;
+    return (pf_wide_units(qkv, my, pf_wide_tiles(qkv, my, m.n_cu), m.n_cu) + pf_wide_units(gu, my, pf_wide_tiles(gu, my, m.n_cu), m.n_cu)) *
+               (m.d / 4096.0) + narrow * (m.hq + m.F) / 4096.0 + 0.5;
+}
+// Row tiles of the next panel of a prompt that has `rows` left, at most max_tiles (<= PF_CUT_TILES): a full panel or the rest, unless
+// another cut of what is left is better by 3 % or more -- then its largest panel.  777 rows of the 13B shape: 7 + 6 tiles
+// (gate/up in 2 + 2 rounds of workgroups) and not 8 + 5 (4 + 2): 72.1 -> 67.8 ms; 2000 rows 42.0 -> 38.6 of 8 layers.  Beyond PF_CUT_TILES tiles the size with the least time per tile.
+constexpr int PF_CUT_TILES = 64;
+inline int pf_next_panel(const PfModel& m, int rows, int max_tiles) {
+    const int R = (rows + PF_ROWS - 1) / PF_ROWS, rest = rows - (R - 1) * PF_ROWS;
+    double cost[PF_CUT_TILES + 1] = {0.0}, best[PF_CUT_TILES + 1] = {0.0};
+    int largest[PF_CUT_TILES + 1] = {0}, even = max_tiles;
+    for (int t = 1; t <= max_tiles; ++t) cost[t] = pf_panel_units(m, t);
+    for (int t = 1; t < max_tiles; ++t)
+        if (cost[t] / t < 0.97 * cost[max_tiles] / max_tiles && cost[t] / t < cost[even] / even) even = t;
+    if (R > PF_CUT_TILES) return even;
+    // a panel of one tile is the last one; of few rows it multiplies one or two of the tile's four column tiles (measured)
+    best[1] = cost[1] * (rest <= 16 ? 0.8 : rest <= 32 ? 0.9 : 1.0);
+    largest[1] = 1;
+    for (int r = 2; r <= R; ++r) {
+        best[r] = 1e300;
+        for (int t = 1; t <= std::min(r, max_tiles); ++t)
+            if (best[r - t] + cost[t] < best[r] - 1e-9) { best[r] = best[r - t] + cost[t]; largest[r] = std::max(t, largest[r - t]); }
+    }
+    const double plain = R / max_tiles * cost[max_tiles] + (R % max_tiles == 1 ? best[1] : cost[R % max_tiles]);
+    return best[R] > 0.97 * plain ? std::min(R, max_tiles) : largest[R];
 }
 
 }  // namespace sdfp
