@@ -329,6 +329,9 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
     // would stall once per step.  What a clamped load brings is never used: the steps a slab does not have are skipped.
     // the wave's weight steps, WD slabs of them: a step's registers take the step WD slabs further on when it is multiplied
     constexpr int WD = pf_weight_depth(NT);
+    // Large tiles (three or four per wave and all columns: bound by the matrix cores) fetch the pieces one slab ahead, behind the
+    // slab's first step: the deeper pipeline of the others is 0.7 % slower there.
+    constexpr bool ONE_AHEAD = WJ == 1 && NT >= 3;
     u32x4 wa[WD][NT][PF_SPS];
     const int last_tile16 = (a.M - 1) >> 4;
     // Slab i into LDS buffer buf; wave w fetches fragments w, w + 8, ...  The loads are counted with the wave's other
@@ -364,12 +367,12 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
     fetch_slab(i_lo, 0);
 #pragma unroll
     for (int s = 0; s < PF_SPS; ++s) load_weight_step(slab_byte0(i_lo), s, wa[0]);
-    fetch_slab(min(i_lo + 1, i_last), 1);
+    if (!ONE_AHEAD) fetch_slab(min(i_lo + 1, i_last), 1);
 #pragma unroll
     for (int w = 1; w < WD; ++w)
 #pragma unroll
         for (int s = 0; s < PF_SPS; ++s) load_weight_step(slab_byte0(min(i_lo + w, i_last)), s, wa[w]);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((WD - 1) * NT * PF_SPS + MIN_FETCH) : "memory");   // the first slab
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ONE_AHEAD ? 0 : (WD - 1) * NT * PF_SPS + MIN_FETCH) : "memory");   // the first slab
     __syncthreads();
     int buf = 0;                                               // LDS slab of slab i
     auto slab = [&](int i, u32x4 (&w)[NT][PF_SPS]) {
@@ -378,7 +381,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
         // The pieces of the slab after the next one, into the buffer whose last readers passed the barrier in front of this
         // slab.  Two slabs ahead and in front of this slab's weight loads: memory answers in order, so the wait for the next
         // slab's pieces at the end of this slab is for nothing younger than the previous slab's start.
-        fetch_slab(min(i + 2, i_last), buf == 0 ? 2 : buf - 1);
+        if (!ONE_AHEAD) fetch_slab(min(i + 2, i_last), buf == 0 ? 2 : buf - 1);
         const char* xb = lds + buf * PF_SLAB_BYTES + j0 * (PF_SPS * PF_FRAG_BYTES) + lane * 16;
         auto frag = [&](int s, int j, int p) {
             return *reinterpret_cast<const u32x4*>(xb + ((p * 4 + j) * PF_SPS + s) * PF_FRAG_BYTES);
@@ -419,6 +422,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
                 for (int p = 0; p < 3; ++p) cur[p] = nxt[p];
             }
             load_weight_step(byte0_next, s, w);           // this step's registers are free
+            if (ONE_AHEAD && s == 0) fetch_slab(min(i + 1, i_last), buf ^ 1);
         }
         if ((i + 1) % nblk == 0) {   // the share's partial sums are complete
             const int p = i / nblk;
@@ -440,9 +444,10 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
         }
         // The next slab's pieces have landed once at most loads issued after them are on their way: this slab's pieces and
         // weights and, with more than one slab of weights ahead, those of the slab before it (the prologue counts as one).
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((WD > 1 ? 2 : 1) * NT * PF_SPS + MIN_FETCH) : "memory");
+        // (ONE_AHEAD: the weights of the three steps behind them).
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ONE_AHEAD ? NT * (PF_SPS - 1) : (WD > 1 ? 2 : 1) * NT * PF_SPS + MIN_FETCH) : "memory");
         __syncthreads();
-        buf = buf == PF_SLABS - 1 ? 0 : buf + 1;
+        buf = ONE_AHEAD ? buf ^ 1 : (buf == PF_SLABS - 1 ? 0 : buf + 1);
     };
     int i = i_lo;
     for (; i + WD <= i_hi; i += WD) {
