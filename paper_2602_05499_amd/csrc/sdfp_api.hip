@@ -105,7 +105,7 @@ struct PanelPlan {
     size_t part_ml_off;    // floats from a region's start to its (max, sum) pairs
     int Ka;                // row length of xs_a: max(d_model, n_heads * head_dim)
 };
-static_assert(PF_TM == PF_ROWS && PF_NSHARE == PF_SHARES, "the plan's tile");
+static_assert(PF_TM == PF_ROWS && PF_NSHARE == PF_SHARES && PF_SPS == PF_STEPS, "the plan's tile");
 constexpr int PANEL_MAX_ROWS = 512, PANEL_MAX_AWG = 512;   // (two attention workgroups per compute unit)
 constexpr size_t PANEL_MAX_BYTES = (size_t)1 << 30;   // a workspace never grows past this for the sake of a larger panel
 // bytes per panel row: residual stream, queries, attention output, reciprocal RMS, the pieces of the two projection

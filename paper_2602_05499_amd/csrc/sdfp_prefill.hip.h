@@ -269,7 +269,6 @@ __global__ __launch_bounds__(256) void k_pf_tile_weights(PfGemm a, bf16_t* __res
 // partial sums P_p to part[p][row][N], and k_pf_residual (k_pf_finish_qkv) adds them in share order.
 // JT: 16-row column tiles of the workgroup tile that are multiplied (4; 1 or 2 for a panel of at most 16 or 32 rows,
 // which then costs a quarter or half of the matrix-core instructions and LDS reads, and fetches as much less).
-constexpr int pf_weight_depth(int nt) { return nt == 1 ? 3 : (nt == 2 ? 2 : 1); }   // slabs of weights in a wave's registers
 template <int KIND, int NT, bool PARTIAL, int JT = 4, int WJ = 1>
 __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -325,13 +324,13 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
         }
 
     // Every load of the loop below is unconditional and its address clamped into the row: a load under a condition makes
-    // the compiler wait, at the join, for everything in flight, and the pipeline (pieces and weights one slab ahead)
-    // would stall once per step.  What a clamped load brings is never used: the steps a slab does not have are skipped.
+    // the compiler wait, at the join, for everything in flight, and the pipeline (pieces one or two slabs ahead, weights up to
+    // three) would stall once per step.  What a clamped load brings is never used: the steps a slab does not have are skipped.
     // the wave's weight steps, WD slabs of them: a step's registers take the step WD slabs further on when it is multiplied
     constexpr int WD = pf_weight_depth(NT);
     // Large tiles (three or four per wave and all columns: bound by the matrix cores) fetch the pieces one slab ahead, behind the
     // slab's first step: the deeper pipeline of the others is 0.7 % slower there.
-    constexpr bool ONE_AHEAD = WJ == 1 && NT >= 3;
+    constexpr bool ONE_AHEAD = pf_one_ahead(NT, WJ);
     u32x4 wa[WD][NT][PF_SPS];
     const int last_tile16 = (a.M - 1) >> 4;
     // Slab i into LDS buffer buf; wave w fetches fragments w, w + 8, ...  The loads are counted with the wave's other
@@ -346,7 +345,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
 #pragma unroll
         for (int u = 0; u < 6; ++u) {
             const int frag = wave_u + u * NWAVE, piece = frag >> 4;
-            if (JT < 4 && ((frag >> 2) & 3) >= JT) continue;   // a column tile that is not multiplied (wave-uniform)
+            if (!pf_fetched(JT, frag)) continue;   // a column tile that is not multiplied (wave-uniform)
             const int tile16 = min((m0 >> 4) + ((frag >> 2) & 3), last_tile16);
             const int step = min((byte0 >> 6) + (frag & 3), S - 1);
             const char* src = xs_base + (size_t)piece * a.xs_piece * 2 + ((size_t)tile16 * S + step) * PF_FRAG_BYTES + lane * 16;
@@ -363,7 +362,6 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
             w[t][s] = *reinterpret_cast<const u32x4*>(wrow[t] + (size_t)(min((byte0 >> 6) + s, S - 1) * wstep));
     };
     const int i_last = i_hi - 1;                               // past the end the last slab is fetched again, unused
-    constexpr int MIN_FETCH = JT == 4 ? 6 : (JT >= 2 ? 3 : 0);   // pieces of a slab that every wave fetches at least
     fetch_slab(i_lo, 0);
 #pragma unroll
     for (int s = 0; s < PF_SPS; ++s) load_weight_step(slab_byte0(i_lo), s, wa[0]);
@@ -372,16 +370,19 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
     for (int w = 1; w < WD; ++w)
 #pragma unroll
         for (int s = 0; s < PF_SPS; ++s) load_weight_step(slab_byte0(min(i_lo + w, i_last)), s, wa[w]);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ONE_AHEAD ? 0 : (WD - 1) * NT * PF_SPS + MIN_FETCH) : "memory");   // the first slab
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(pf_wait_first(NT, JT, WJ)) : "memory");
     __syncthreads();
     int buf = 0;                                               // LDS slab of slab i
-    auto slab = [&](int i, u32x4 (&w)[NT][PF_SPS]) {
+    // tail: the walk's last slabs, behind whole rounds of WD; their pieces and weights are on their way or here, there is
+    // nothing more to request.
+    auto slab = [&](int i, u32x4 (&w)[NT][PF_SPS], auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;
         const int nst = slab_steps(i);
         const int byte0_next = slab_byte0(min(i + WD, i_last));
         // The pieces of the slab after the next one, into the buffer whose last readers passed the barrier in front of this
         // slab.  Two slabs ahead and in front of this slab's weight loads: memory answers in order, so the wait for the next
         // slab's pieces at the end of this slab is for nothing younger than the previous slab's start.
-        if (!ONE_AHEAD) fetch_slab(min(i + 2, i_last), buf == 0 ? 2 : buf - 1);
+        if (!ONE_AHEAD && !TAIL) fetch_slab(min(i + 2, i_last), buf == 0 ? 2 : buf - 1);
         const char* xb = lds + buf * PF_SLAB_BYTES + j0 * (PF_SPS * PF_FRAG_BYTES) + lane * 16;
         auto frag = [&](int s, int j, int p) {
             return *reinterpret_cast<const u32x4*>(xb + ((p * 4 + j) * PF_SPS + s) * PF_FRAG_BYTES);
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
 #pragma unroll
                 for (int p = 0; p < 3; ++p) cur[p] = nxt[p];
             }
-            load_weight_step(byte0_next, s, w);           // this step's registers are free
+            if (!TAIL) load_weight_step(byte0_next, s, w);           // this step's registers are free
             if (ONE_AHEAD && s == 0) fetch_slab(min(i + 1, i_last), buf ^ 1);
         }
         if ((i + 1) % nblk == 0) {   // the share's partial sums are complete
@@ -442,21 +443,29 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_pf_gemm(PfGemm a) {
                     acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
         }
-        // The next slab's pieces have landed once at most loads issued after them are on their way: this slab's pieces and
-        // weights and, with more than one slab of weights ahead, those of the slab before it (the prologue counts as one).
-        // (ONE_AHEAD: the weights of the three steps behind them).
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ONE_AHEAD ? NT * (PF_SPS - 1) : (WD > 1 ? 2 : 1) * NT * PF_SPS + MIN_FETCH) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TAIL ? 0 : pf_wait_slab(NT, JT, WJ)) : "memory");   // the next slab's pieces
         __syncthreads();
         buf = ONE_AHEAD ? buf ^ 1 : (buf == PF_SLABS - 1 ? 0 : buf + 1);
     };
     int i = i_lo;
     for (; i + WD <= i_hi; i += WD) {
 #pragma unroll
-        for (int w = 0; w < WD; ++w) slab(i + w, wa[w]);
+        for (int w = 0; w < WD; ++w) slab(i + w, wa[w], std::false_type{});
     }
 #pragma unroll
     for (int w = 0; w + 1 < WD; ++w)
-        if (i + w < i_hi) slab(i + w, wa[w]);
+        if (i + w < i_hi) slab(i + w, wa[w], std::true_type{});
+    // Pieces fetched past the end have landed before the workgroup gives its LDS back.  And every weight load above has a use,
+    // here: one that brings nothing that is multiplied could be dropped otherwise, and the waits count it.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (WD > 1) {
+#pragma unroll
+        for (int w = 0; w < WD; ++w)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int s = 0; s < PF_SPS; ++s) asm volatile("" ::"v"(wa[w][t][s]));
+    }
     if (PARTIAL) return;
 
     // ---- epilogue.  Lane l holds, per tile, prompt row (column) l % 16 and output rows 4 * (l / 16) .. + 3 of the tile.

@@ -1,4 +1,5 @@
-// The cut of a prompt into panels, the tiles of its GEMMs, and which kernel runs a panel's attention (host arithmetic only).
+// The cut of a prompt into panels, the tiles of its GEMMs and the counts of their pipeline, and which kernel runs a panel's
+// attention (host arithmetic only).
 #pragma once
 #include <algorithm>
 
@@ -87,6 +88,27 @@ inline bool pf_attn_on_matrix_cores(const PfAttnPanel& p) {
     return pf_chunk_splits(p, (p.M - 1) / PF_CHUNK) > PF_VALU_MAX_SPLITS || pf_mx_us(p) <= pf_valu_us(p);
 }
 
+// ---- the pipeline of k_pf_gemm<.., NT, .., JT, WJ>: what a wave has requested and not received when it waits.  Memory answers a
+// wave in order, so a wait that lets n loads be on their way is over when all but the last n are here.  The waits below hold only
+// if every load they count is issued: the kernel's last slabs, which request nothing, wait for everything instead.
+constexpr int PF_STEPS = 4;   // steps of a slab: one weight load each per tile, and fragments of the pieces per column tile
+constexpr int pf_weight_depth(int nt) { return nt == 1 ? 3 : (nt == 2 ? 2 : 1); }   // slabs of weights in a wave's registers
+constexpr bool pf_one_ahead(int nt, int wj) { return wj == 1 && nt >= 3; }          // pieces one slab ahead, not two
+// fragment = (piece * 4 + column tile) * 4 + step of a slab; wave w fetches fragments w, w + 8, .. of the column tiles it needs
+constexpr bool pf_fetched(int jt, int fragment) { return ((fragment >> 2) & 3) < jt; }
+constexpr int pf_min_fetch(int jt) { return jt == 4 ? 6 : (jt >= 2 ? 3 : 0); }      // of a slab, by every wave, at least
+// Prologue: pieces of the first slab and its weights, pieces of the second (unless one ahead), the other slabs' weights.  What may
+// be on its way when the first slab is read: everything behind its weights.
+constexpr int pf_wait_first(int nt, int jt, int wj) {
+    return pf_one_ahead(nt, wj) ? 0 : (pf_weight_depth(nt) - 1) * nt * PF_STEPS + pf_min_fetch(jt);
+}
+// A slab: pieces of the slab after the next one, then a weight load per step and tile.  What may be on its way when the next slab
+// is read: this slab's requests and, with more than one slab of weights ahead, the weights requested behind the next slab's
+// pieces (the prologue has as many).  One ahead: the pieces of the next slab come behind the first step, so the weights of the
+// steps after it.
+constexpr int pf_wait_slab(int nt, int jt, int wj) {
+    return pf_one_ahead(nt, wj) ? nt * (PF_STEPS - 1) : (pf_weight_depth(nt) > 1 ? 2 : 1) * nt * PF_STEPS + pf_min_fetch(jt);
+}
 
 // ---- tiles and panels of the GEMMs.  A launch takes whole rounds of workgroups on the compute units, one each; its time in
 // UNITS: one unit = a round of workgroups with one weight tile per wave over a reduction of 4096, 38 us.
