@@ -249,10 +249,12 @@ __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* 
                 st_coh(a.att + (size_t)hq * hd + dim, fmaf(w, o, 0.f) / fmaf(w, mls[ql * 2 + 1], 0.f));
                 continue;
             }
-            st_coh(a.part_o + (((size_t)split * MAX_ROWS + m) * part_H + hq - part_h0) * hd + dim, o);
+            // (the panel's partials are not polled)
+            auto partial = [](float v) { return PANEL ? v : not_armed(v); };
+            st_coh(a.part_o + (((size_t)split * MAX_ROWS + m) * part_H + hq - part_h0) * hd + dim, partial(o));
             if (dim == 0) {
                 float* ml = a.part_ml + (((size_t)split * MAX_ROWS + m) * part_H + hq - part_h0) * 2;
-                st_coh(ml, mls[ql * 2]); st_coh(ml + 1, mls[ql * 2 + 1]);
+                st_coh(ml, partial(mls[ql * 2])); st_coh(ml + 1, partial(mls[ql * 2 + 1]));
             }
         }
         __syncthreads();

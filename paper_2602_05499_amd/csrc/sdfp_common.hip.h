@@ -225,8 +225,9 @@ constexpr int BAR_FLAG_OFF = BAR_STRIDE;
 // Hand-over of activations by the data itself: the buffers that one phase writes and the next projection reads are
 // pre-armed with this bit pattern at the start of a forward, are written once, and a reader polls until none of
 // its values still holds it.  It is a NaN that arithmetic does not produce (hardware makes the canonical quiet NaN);
-// only a NaN with this very payload in the caller's weights could imitate it, and then the bounded wait ends the
-// forward with the time-out flag instead of a result.
+// only a NaN with this very payload in the caller's weights could imitate it: in row 0 of a decode forward's hand-over buffers
+// the bounded wait then ends the forward with the time-out flag instead of a result; the attention's partials, which are polled
+// in every row and by prompt chunks too, are kept from it (not_armed).
 constexpr unsigned HANDOVER_ARMED = 0xFFFFFFFFu;
 __device__ __forceinline__ bool armed4(const f32x4& a) {
     return max(max(__float_as_uint(a.x), __float_as_uint(a.y)), max(__float_as_uint(a.z), __float_as_uint(a.w))) == HANDOVER_ARMED;
@@ -235,6 +236,8 @@ __device__ __forceinline__ f32x4 armed_quad() {
     const float a = __uint_as_float(HANDOVER_ARMED);
     return f32x4{a, a, a, a};
 }
+// A value that is handed over behind the mark whatever it was computed from: the mark itself becomes the NaN next to it.
+__device__ __forceinline__ float not_armed(float v) { return __uint_as_float(min(__float_as_uint(v), HANDOVER_ARMED - 1u)); }
 __device__ __forceinline__ bool armed8(const f32x4& a, const f32x4& b) {   // any of the 8 values not written yet
     const unsigned m0 = max(max(__float_as_uint(a.x), __float_as_uint(a.y)), max(__float_as_uint(a.z), __float_as_uint(a.w)));
     const unsigned m1 = max(max(__float_as_uint(b.x), __float_as_uint(b.y)), max(__float_as_uint(b.z), __float_as_uint(b.w)));
