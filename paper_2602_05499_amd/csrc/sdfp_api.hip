@@ -107,6 +107,7 @@ struct PanelPlan {
 };
 static_assert(PF_TM == PF_ROWS && PF_NSHARE == PF_SHARES && PF_SPS == PF_STEPS, "the plan's tile");
 constexpr int PANEL_MAX_ROWS = 512, PANEL_MAX_AWG = 512;   // (two attention workgroups per compute unit)
+static_assert(PANEL_MAX_ROWS / PF_ROWS <= PF_CUT_TILES, "a cut holds at least one panel");
 constexpr size_t PANEL_MAX_BYTES = (size_t)1 << 30;   // a workspace never grows past this for the sake of a larger panel
 // bytes per panel row: residual stream, queries, attention output, reciprocal RMS, the pieces of the two projection
 // inputs, and the 8 per-share partial sums of an O / down projection
@@ -635,11 +636,7 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
     int e;
     float* shares = reinterpret_cast<float*>(base + pl.shares);
     // O / down projections have few outputs: deal a tile's shares to as many workgroups as it takes to fill the chip
-    auto share_groups = [&](int n_nt, int my) {
-        int gcount = 1;
-        while (gcount < PF_NSHARE && n_nt * my * gcount < (c->n_cu * 3) / 4) gcount *= 2;
-        return gcount;
-    };
+    auto share_groups = [&](int n_nt, int my) { return pf_share_groups(n_nt, my, c->n_cu); };
     auto gemm_grid = [](const PfGemm& a) { return dim3((unsigned)((a.n_nt * a.n_groups + 7) / 8 * 8 * a.my)); };
     const TiledLayout tl = tiled_layout(g);
     auto tiled_at = [&](int l, size_t off) {
@@ -647,15 +644,18 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
     };
     // weight tiles per wave: 3 (QKV, gate/up) or 4 (O, down) when the panel has rows enough to fill the chip with such
     // tiles, else 1 (a short prompt is bound by the read of the weights and wants many workgroups, not large tiles)
-    constexpr int NT_WIDE = 3, NT_NARROW = 4;
-    // (measured on the 7B shape: the one-tile kernels win only below about 3/8 of the compute units' worth of large
-    // tiles -- they read as many LDS bytes per matrix-core step as they feed it)
-    auto tiles_fill = [&](int n_tiles, int nt, int my, int groups) {
-        return ((n_tiles + 8 * nt - 1) / (8 * nt)) * my * groups >= (c->n_cu * 3) / 8;
-    };
+    constexpr int NT_NARROW = 4;
+    auto tiles_fill = [&](int n_tiles, int my) { return pf_tiles_fill(n_tiles, my, c->n_cu); };
     auto pick_nt = [&](int n_tiles, int my) { return pf_wide_tiles(n_tiles, my, c->n_cu); };
-    for (int p0 = 0, np = 0; p0 < n; p0 += np) {
-        np = std::min(n - p0, PF_TM * pf_next_panel(PfModel{d, hq, hkv, F, c->n_cu}, n - p0, pl.P / PF_TM));
+    // Split partials of k_pf_attn_mx: the room of the projections' partial sums (idle then) or the regions of k_pf_attn's
+    // workgroups, whichever is larger -- never none: 8 regions hold 128 grp >= 64 queries.  With fewer slots than items a workgroup
+    // takes several items.
+    const size_t in_shares = (size_t)PF_NSHARE * pl.P * d, in_part = (size_t)pl.n_awg * pl.part_stride;
+    const PfModel model{d, hq, hkv, F, c->n_cu, g.head_dim, pl.P / PF_TM, pl.n_awg, std::max(in_shares, in_part)};
+    PfCut cut{0, {}};
+    for (int p0 = 0, np = 0, at = 0; p0 < n; p0 += np, ++at) {
+        if (at == cut.n) { cut = pf_cut(model, n - p0, p0); at = 0; }
+        np = std::min(n - p0, PF_TM * cut.tiles[at]);
         const dim3 blk(WG_THREADS);
         // the share sums of a projection of `outs` outputs fit the scratch that is sized for the panel's O / down sums
         auto dealt_fits = [&](int outs) { return (size_t)np * outs <= (size_t)pl.P * d; };
@@ -713,26 +713,18 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             t.q = q; t.att = att; t.kc = kc; t.vc = vc;
             t.part = reinterpret_cast<float*>(base + pl.part); t.part_stride = pl.part_stride; t.part_ml_off = pl.part_ml_off;
             t.M = np; t.pos0 = p0; t.L = L;
-            const int n_chunks = (np + MAX_ROWS - 1) / MAX_ROWS, grp = g.n_heads / g.n_kv_heads;
-            const int n_act = (p0 + np + ATT_SL - 1) / ATT_SL;
+            const int n_chunks = (np + MAX_ROWS - 1) / MAX_ROWS, n_act = (p0 + np + ATT_SL - 1) / ATT_SL;
             // Attention on the matrix cores (head_dim 64 and 128) or on the vector ALUs: whichever the times of
             // sdfp_prefill_plan.h say is quicker for this panel.
-            // Split partials of the former: the room of the projections' partial sums (idle here) or the regions of
-            // k_pf_attn's workgroups, whichever holds more slots -- never none: 8 regions hold 128 grp >= 64 queries.  With
-            // fewer slots than items a workgroup takes several items.
-            const size_t slot = pfx_slot_floats(g.head_dim, n_act);
-            const size_t in_shares = (size_t)PF_NSHARE * pl.P * d / slot, in_part = (size_t)pl.n_awg * pl.part_stride / slot;
-            const size_t items = (size_t)((n_chunks * grp + PFX_TILES - 1) / PFX_TILES) * g.n_kv_heads;
-            const int n_wg = (int)std::min(items, std::max(in_shares, in_part));
-            if (g.head_dim >= 64 &&
-                pf_attn_on_matrix_cores(PfAttnPanel{g.head_dim, g.n_kv_heads, grp, np, p0, c->n_cu, pl.n_awg, n_wg})) {
+            const PfAttnPanel panel = pf_attn_panel(model, np, p0);
+            if (pf_attn_on_matrix_cores(panel)) {
                 PfAttnMx x;
                 std::memset(&x, 0, sizeof(x));
                 x.q = q; x.att = att; x.kc = kc; x.vc = vc; x.M = np; x.pos0 = p0; x.L = L;
-                x.part_stride = slot;
+                x.part_stride = pf_mx_slot_floats(g.head_dim, n_act);
                 x.part_ml_off = (size_t)n_act * PFX_QUERIES * g.head_dim;
                 x.part = in_shares >= in_part ? shares : t.part;
-                if ((e = launch_pf_attn_mx(c, x, n_wg))) return e;
+                if ((e = launch_pf_attn_mx(c, x, panel.wg_mx))) return e;
             } else if ((e = launch_pf_attn(c, t, std::min(pl.n_awg, n_chunks * g.n_kv_heads)))) {
                 return e;
             }
@@ -740,8 +732,8 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             a.w[0] = (const bf16_t*)lp.wo; a.w[1] = a.w[2] = nullptr;
             a.xs = xs_a; a.xs_piece = pf_xs_piece(np, hq); a.Kd = hq; a.n_tiles = d / 16; a.rs = nullptr; a.h = h;
             a.wt = tiled_at(l, tl.o);
-            if (tiles_fill(a.n_tiles, NT_NARROW, my, PF_NSHARE)) {
-                a.n_nt = (a.n_tiles + 8 * NT_NARROW - 1) / (8 * NT_NARROW); a.n_groups = pf_narrow_groups(a.n_nt * my, c->n_cu);
+            if (tiles_fill(a.n_tiles, my)) {
+                a.n_nt = (a.n_tiles + 8 * NT_NARROW - 1) / (8 * NT_NARROW); a.n_groups = pf_narrow_groups(a.n_nt, my, c->n_cu);
                 e = launch_pf(c, k_pf_gemm<PF_OPROJ, NT_NARROW, true>, gemm_grid(a), blk, PF_LDS_BYTES, a);
             } else {
                 a.n_nt = (a.n_tiles + 7) / 8; a.n_groups = share_groups(a.n_nt, my);
@@ -775,8 +767,8 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
             a.w[0] = (const bf16_t*)lp.wd; a.w[1] = nullptr;
             a.xs = xs_b; a.xs_piece = pf_xs_piece(np, F); a.Kd = F; a.n_tiles = d / 16; a.rs = nullptr;
             a.wt = tiled_at(l, tl.down);
-            if (tiles_fill(a.n_tiles, NT_NARROW, my, PF_NSHARE)) {
-                a.n_nt = (a.n_tiles + 8 * NT_NARROW - 1) / (8 * NT_NARROW); a.n_groups = pf_narrow_groups(a.n_nt * my, c->n_cu);
+            if (tiles_fill(a.n_tiles, my)) {
+                a.n_nt = (a.n_tiles + 8 * NT_NARROW - 1) / (8 * NT_NARROW); a.n_groups = pf_narrow_groups(a.n_nt, my, c->n_cu);
                 e = launch_pf(c, k_pf_gemm<PF_DOWN, NT_NARROW, true>, gemm_grid(a), blk, PF_LDS_BYTES, a);
             } else {
                 a.n_nt = (a.n_tiles + 7) / 8; a.n_groups = share_groups(a.n_nt, my);

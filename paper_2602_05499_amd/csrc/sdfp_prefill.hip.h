@@ -670,7 +670,6 @@ static_assert(PF_CHUNK == MAX_ROWS && PF_SPLIT == ATT_SL, "the plan's cuts are t
 static_assert(PF_VALU_MAX_SPLITS * 8 <= attn_lds_bytes(16, 0, ATT_QC_PANEL, true) && PF_VALU_MAX_SPLITS * 8 <= attn_lds_bytes(32, 0, ATT_QC_PANEL, true) &&
               PF_VALU_MAX_SPLITS * 8 <= attn_lds_bytes(64, 0, ATT_QC_PANEL, true), "one query's statistics fit k_pf_attn's LDS");
 __host__ __device__ constexpr size_t pfx_lds_bytes(int hd) { return (size_t)2 * 2 * ATT_SL * hd * 2; }   // 2 splits x (K, V)
-__host__ __device__ constexpr size_t pfx_slot_floats(int hd, int n_splits) { return (size_t)n_splits * PFX_QUERIES * (hd + 2); }
 
 __device__ __forceinline__ f32x4 add4_rn(const f32x4& a, const f32x4& b) {
     return f32x4{add_rn(a.x, b.x), add_rn(a.y, b.y), add_rn(a.z, b.z), add_rn(a.w, b.w)};

@@ -2,6 +2,7 @@
 // attention (host arithmetic only).
 #pragma once
 #include <algorithm>
+#include <cstddef>
 
 namespace sdfp {
 
@@ -111,15 +112,21 @@ constexpr int pf_wait_slab(int nt, int jt, int wj) {
 }
 
 // ---- tiles and panels of the GEMMs.  A launch takes whole rounds of workgroups on the compute units, one each; its time in
-// UNITS: one unit = a round of workgroups with one weight tile per wave over a reduction of 4096, 38 us.
+// UNITS: one unit = a round of workgroups with one weight tile per wave over a reduction of 4096, 36 us.
 constexpr int PF_SHARES = 8, PF_ROWS = 64;   // shares of the reduction dimension, prompt rows per workgroup tile
 
-inline double pf_rounds(int wgs, int n_cu) { return (double)((wgs + n_cu - 1) / n_cu); }
-// QKV and gate/up with nt tiles per wave (and half the columns each at nt < 3): smaller tiles read more bytes per matrix-core
-// instruction (measured per tile at 512 rows: 37.6 us with three, 39.8 with two; at a reduction of 8192 the ratio is 1.14).
+// A column (tile group and share group) and its my row tiles lie on one XCD, columns are dealt to the eight in turn: 36 columns
+// of 7 row tiles are 252 workgroups, but 35 on some XCDs' 32 compute units, two rounds (d 2560, gate/up: 153 us; 6 row tiles 85).
+inline double pf_rounds(int columns, int my, int n_cu) {
+    const int per_xcd = (columns + 7) / 8 * my, cu = std::max(1, n_cu / 8);
+    return (double)((per_xcd + cu - 1) / cu);
+}
+// QKV and gate/up with 8 nt tiles per workgroup (nt per wave; at nt < 3 twice as many and half the columns): smaller tiles read more
+// bytes per matrix-core instruction (us per round, tile and reduction of 4096, d 4096 to 8192: 34-37 with three, 37-41 with two,
+// 49-54 with one).
 inline double pf_wide_units(int n_tiles, int my, int nt, int n_cu) {
     const double w[4] = {0.0, 1.4, 1.1, 1.0};
-    return pf_rounds((n_tiles + 8 * nt - 1) / (8 * nt) * my, n_cu) * nt * w[nt];
+    return pf_rounds((n_tiles + 8 * nt - 1) / (8 * nt), my, n_cu) * nt * w[nt];
 }
 // 290 workgroups of 3 tiles are two rounds, 430 of 2 tiles two cheaper ones; 116 of 3 tiles fill half the chip, 172 of 2 tiles
 // two thirds of it in two thirds of the time.
@@ -132,43 +139,110 @@ inline int pf_wide_tiles(int n_tiles, int my, int n_cu) {
 // O and down projection in tiles of 4 per wave: a tile's shares dealt to g workgroups, each with its prologue and its way out
 // (a fifth of a share of 4096).  80 workgroups (5120 outputs, 512 rows): 4 groups are 320 workgroups of two shares, two rounds
 // = 4.4 shares, 8 groups three rounds = 3.6.
-inline double pf_narrow_shares(int wgs, int g, int n_cu) { return pf_rounds(wgs * g, n_cu) * ((double)PF_SHARES / g + 0.2); }
-inline int pf_narrow_groups(int wgs, int n_cu) {
+inline double pf_narrow_shares(int n_nt, int my, int g, int n_cu) {
+    return pf_rounds(n_nt * g, my, n_cu) * ((double)PF_SHARES / g + 0.2);
+}
+inline int pf_narrow_groups(int n_nt, int my, int n_cu) {
     int best = 1;
     for (int g = 2; g <= PF_SHARES; g *= 2)
-        if (pf_narrow_shares(wgs, g, n_cu) < pf_narrow_shares(wgs, best, n_cu) - 1e-9) best = g;
+        if (pf_narrow_shares(n_nt, my, g, n_cu) < pf_narrow_shares(n_nt, my, best, n_cu) - 1e-9) best = g;
     return best;
 }
-struct PfModel { int d, hq, hkv, F, n_cu; };
-// A layer's GEMMs over my row tiles, and half a unit for what a panel costs besides.
-inline double pf_panel_units(const PfModel& m, int my) {
-    const int qkv = (m.hq + 2 * m.hkv) / 16, gu = m.F / 8, out = (m.d + 511) / 512 * my;
-    const double narrow = pf_narrow_shares(out, pf_narrow_groups(out, m.n_cu), m.n_cu) * 4.0 / PF_SHARES;
-    return (pf_wide_units(qkv, my, pf_wide_tiles(qkv, my, m.n_cu), m.n_cu) + pf_wide_units(gu, my, pf_wide_tiles(gu, my, m.n_cu), m.n_cu)) *
-               (m.d / 4096.0) + narrow * (m.hq + m.F) / 4096.0 + 0.5;
+// A tile's shares dealt to workgroups of one-tile kernels (short panels; QKV is finished by a kernel of its own).
+inline int pf_share_groups(int n_nt, int my, int n_cu) {
+    int g = 1;
+    while (g < PF_SHARES && n_nt * my * g < (n_cu * 3) / 4) g *= 2;
+    return g;
 }
-// Row tiles of the next panel of a prompt that has `rows` left, at most max_tiles (<= PF_CUT_TILES): a full panel or the rest, unless
-// another cut of what is left is better by 3 % or more -- then its largest panel.  777 rows of the 13B shape: 7 + 6 tiles
-// (gate/up in 2 + 2 rounds of workgroups) and not 8 + 5 (4 + 2): 72.1 -> 67.8 ms; 2000 rows 42.0 -> 38.6 of 8 layers.  Beyond PF_CUT_TILES tiles the size with the least time per tile.
+// O and down: tiles of 4 per wave when they fill the chip, else of one (measured on the 7B shape: those win only below about 3/8
+// of the compute units' worth of large tiles -- they read as many LDS bytes per matrix-core step as they feed it)
+inline bool pf_tiles_fill(int n_tiles, int my, int n_cu) { return (n_tiles + 31) / 32 * my * PF_SHARES >= (n_cu * 3) / 8; }
+
+struct PfModel {
+    int d, hq, hkv, F, n_cu, hd;
+    int max_tiles;     // row tiles of the largest panel that the workspace holds
+    int wg_valu;       // workgroups k_pf_attn may use (regions of split partials)
+    size_t mx_room;    // floats for the split partials of k_pf_attn_mx
+};
+// A panel of k_pf_attn_mx: split partials and their statistics of one workgroup, and the workgroups there is room for
+constexpr size_t pf_mx_slot_floats(int hd, int n_splits) { return (size_t)n_splits * PF_MX_TILES * PF_CHUNK * (hd + 2); }
+inline PfAttnPanel pf_attn_panel(const PfModel& m, int rows, int pos0) {
+    PfAttnPanel p{m.hd, m.hkv / m.hd, m.hq / m.hkv, rows, pos0, m.n_cu, m.wg_valu, 0};
+    if (m.hd < 64) return p;   // no instance
+    const size_t slots = m.mx_room / pf_mx_slot_floats(m.hd, pf_chunk_splits(p, (rows - 1) / PF_CHUNK));
+    const size_t items = (size_t)(((rows + PF_CHUNK - 1) / PF_CHUNK * p.grp + PF_MX_TILES - 1) / PF_MX_TILES) * p.Hkv;
+    p.wg_mx = (int)std::min(items, slots);
+    return p;
+}
+// A layer's time in us for a panel, from its kernels' times at 64 to 512 rows of eight shapes; over sixteen shapes, d 512 to 8192,
+// it is 5 % off on average.
+// A reduction takes whole blocks of 1024 values (d 2560 as long as 3072).  One block of one tile per wave: 8.6 us a round of
+// workgroups (three tiles, d 4096: 103-115 us a round, 209-229 two), and 3 us a round for its prologue and way out.  What lies
+// between the GEMMs: 20 us and the rows' way through memory.
+constexpr double PF_BLOCK_US = 8.6, PF_ROUND_US = 3.0;
+inline double pf_gemms_us(const PfModel& m, int my) {
+    auto blocks = [](int K) { return (K + 1023) / 1024; };
+    auto dealt = [&](int n_tiles, int K) {
+        const int wgs = (n_tiles + 7) / 8, g = pf_share_groups(wgs, my, m.n_cu);
+        return pf_rounds(wgs * g, my, m.n_cu) * (PF_SHARES / g) * 0.2 * PF_BLOCK_US * blocks(K) + 2 * PF_ROUND_US;
+    };
+    auto wide = [&](int n_tiles, int K) {
+        const int nt = pf_wide_tiles(n_tiles, my, m.n_cu);
+        return pf_wide_units(n_tiles, my, nt, m.n_cu) * PF_BLOCK_US * blocks(K) +
+               pf_rounds((n_tiles + 8 * nt - 1) / (8 * nt), my, m.n_cu) * PF_ROUND_US;
+    };
+    auto narrow = [&](int K) {
+        if (!pf_tiles_fill(m.d / 16, my, m.n_cu)) return dealt(m.d / 16, K);
+        const int n_nt = (m.d / 16 + 31) / 32;
+        return pf_narrow_shares(n_nt, my, pf_narrow_groups(n_nt, my, m.n_cu), m.n_cu) * 0.5 * PF_BLOCK_US * blocks(K) + PF_ROUND_US;
+    };
+    const int outs = m.hq + 2 * m.hkv, qkv_tiles = outs / 16;
+    const bool qkv_dealt = pf_wide_tiles(qkv_tiles, my, m.n_cu) == 1 && pf_share_groups((qkv_tiles + 7) / 8, my, m.n_cu) > 1;
+    return (qkv_dealt ? dealt(qkv_tiles, m.d) + 2 * PF_ROUND_US : wide(qkv_tiles, m.d)) + narrow(m.hq) + wide(m.F / 8, m.d) + narrow(m.F);
+}
+inline double pf_panel_us(const PfModel& m, int rows, int pos0, double gemms_us) {
+    // of few rows one or two of the tile's four column tiles are multiplied
+    const double few = rows <= 16 ? 0.8 : rows <= 32 ? 0.9 : 1.0;
+    const PfAttnPanel p = pf_attn_panel(m, rows, pos0);
+    const double mx = p.wg_mx > 0 ? pf_mx_us(p) : 1e300, valu = pf_valu_us(p);
+    return few * gemms_us + std::min(mx, valu) + 20.0 + 1.1 * (rows / (double)PF_ROWS) * (m.d / 1024.0);
+}
+// The cut of `rows` rows from position pos0 into panels: full panels and a rest, unless the best cut is better by 2.5 % or more.  777
+// rows of the 13B shape (4 layers) as 7 + 6 tiles and not 8 + 5: 6.66 -> 6.26 ms, gate/up in 2 + 2 rounds of workgroups and not
+// 4 + 2; 1100 of the 7B shape as 2 + 8 + 8: 6.65 -> 6.28 (attention behind 8 splits costs a few rows what it costs a full panel).
+// Over 20 shapes, d 512 to 8192, and 17 lengths from 513 to 4096 no cut that is chosen was slower than full panels, those that
+// differ are 5 to 6 % quicker; without attention and the XCDs in the model the same rule lost up to 23 % (d 2560, 3500 rows).
+// Long prompts are cut PF_CUT_TILES row tiles at a time (the caller comes again with what is left): up to 70 us of host work, in
+// front of the first panel, and beside the GPU's from then on.
 constexpr int PF_CUT_TILES = 64;
-inline int pf_next_panel(const PfModel& m, int rows, int max_tiles) {
-    const int R = (rows + PF_ROWS - 1) / PF_ROWS, rest = rows - (R - 1) * PF_ROWS;
-    double cost[PF_CUT_TILES + 1] = {0.0}, best[PF_CUT_TILES + 1] = {0.0};
-    int largest[PF_CUT_TILES + 1] = {0}, even = max_tiles;
-    for (int t = 1; t <= max_tiles; ++t) cost[t] = pf_panel_units(m, t);
-    for (int t = 1; t < max_tiles; ++t)
-        if (cost[t] / t < 0.97 * cost[max_tiles] / max_tiles && cost[t] / t < cost[even] / even) even = t;
-    if (R > PF_CUT_TILES) return even;
-    // a panel of one tile is the last one; of few rows it multiplies one or two of the tile's four column tiles (measured)
-    best[1] = cost[1] * (rest <= 16 ? 0.8 : rest <= 32 ? 0.9 : 1.0);
-    largest[1] = 1;
-    for (int r = 2; r <= R; ++r) {
+struct PfCut { int n; int tiles[PF_CUT_TILES]; };
+inline PfCut pf_cut(const PfModel& m, int rows, int pos0) {
+    const int all = (rows + PF_ROWS - 1) / PF_ROWS, P = m.max_tiles;
+    const int R = all <= PF_CUT_TILES ? all : PF_CUT_TILES / P * P;   // (P <= 8)
+    PfCut c{0, {}};
+    double gemms[PF_CUT_TILES + 1];
+    for (int t = 1; t <= std::min(R, P); ++t) gemms[t] = pf_gemms_us(m, t);
+    auto us = [&](int from, int t) {
+        return pf_panel_us(m, std::min(t * PF_ROWS, rows - from * PF_ROWS), pos0 + from * PF_ROWS, gemms[t]);
+    };
+    double best[PF_CUT_TILES + 1] = {0.0}, plain = 0.0;
+    int last[PF_CUT_TILES + 1] = {0};
+    for (int r = 1; r <= R; ++r) {
         best[r] = 1e300;
-        for (int t = 1; t <= std::min(r, max_tiles); ++t)
-            if (best[r - t] + cost[t] < best[r] - 1e-9) { best[r] = best[r - t] + cost[t]; largest[r] = std::max(t, largest[r - t]); }
+        for (int t = std::min(r, P); t >= 1; --t) {
+            const double v = best[r - t] + us(r - t, t);
+            if (v < best[r] - 1e-9) { best[r] = v; last[r] = t; }
+        }
     }
-    const double plain = R / max_tiles * cost[max_tiles] + (R % max_tiles == 1 ? best[1] : cost[R % max_tiles]);
-    return best[R] > 0.97 * plain ? std::min(R, max_tiles) : largest[R];
+    for (int r = 0; r < R; r += P) plain += us(r, std::min(P, R - r));
+    const bool other = best[R] <= 0.975 * plain;
+    for (int r = R; r > 0; ++c.n) {   // from the end
+        const int rest = R % P == 0 ? P : R % P, t = other ? last[r] : (c.n == 0 ? rest : P);
+        c.tiles[c.n] = t;
+        r -= t;
+    }
+    std::reverse(c.tiles, c.tiles + c.n);
+    return c;
 }
 
 }  // namespace sdfp

@@ -111,20 +111,18 @@ def test_matrix_prompt_path_at_other_baseline_widths(gpu, name, n):
 
 
 @pytest.mark.timeout(900)
-@pytest.mark.parametrize("name,lengths", [("13b", [512, 513, 777, 2000]), ("l3-8b", [576]), ("small", [600, 1100])])
+@pytest.mark.parametrize("name,lengths", [("13b", [512, 513, 777, 2000]), ("small", [600, 1100]), ("d2560", [1100])])
 def test_panels_that_are_not_full_ones_and_a_rest(gpu, tmp_path, name, lengths):
     """Cuts by rounds of workgroups: panels shorter than the workspace's that are not the last, panels that start inside an
-    attention split (position 448, 320), O and down shares dealt to eight groups (13B, 512 rows).  Two layers each."""
+    attention split (position 448, 192), O and down shares dealt to eight groups (13B, 512 rows).  Two layers each."""
     dims = panels.MODELS[name]
-    if name == "small":
-        s = synth.CONFIGS["tiny"].with_(name="d1024-2layers", dtype="bf16", d_model=1024, n_heads=16, n_kv_heads=4, head_dim=64, d_ffn=2816,
-                                        n_layers=2, n_skip=1, skip_layers=(1,), gain_std=0.1, init_std=0.05)
-    else:
-        s = synth.CONFIGS[name].with_(name=name + "-2layers", n_layers=2, n_skip=1, gain_std=0.1)
-    assert dims == (s.d_model, s.n_heads * s.head_dim, s.n_kv_heads * s.head_dim, s.d_ffn)
+    d, H, Hkv, hd, F = dims
+    s = synth.CONFIGS["tiny"].with_(name=name + "-2layers", dtype="bf16", d_model=d, n_heads=H, n_kv_heads=Hkv, head_dim=hd, d_ffn=F,
+                                    n_layers=2, n_skip=1, skip_layers=(1,), gain_std=0.1, init_std=0.05)
     plan = panels.compile_plan(tmp_path)
-    cuts = {n: panels.cut(plan, dims, n) for n in lengths}
+    cuts = {n: panels.cut(plan, dims, n, max_seq=max(lengths) + 16) for n in lengths}
     assert all(cuts[n] != panels.full_panels_and_a_rest(n) for n in lengths if n != 512), cuts
+    assert name != "13b" or cuts[777] == [7, 6] and cuts[513] == [3, 6]
     _both_paths(gpu, s, lengths)
 
 
