@@ -71,7 +71,8 @@ template <> struct Row4<float> {
 // of once per query (there are registers for it here).  (Skipping the row loads whose positions all lie beyond the
 // chunk's last row was tried: the branches cost more than the work they save.)  false (forward kernels): all heads;
 // these kernels have no register to spare for any of that.
-// LONGCTX (PANEL): the panel ends beyond 8 splits: merge_long (statistics staged in LDS, partials in batches).
+// LONGCTX (PANEL): the panel ends beyond 8 splits, and a chunk beyond them is merged by merge_long (statistics staged in LDS,
+// partials in batches); without it no chunk may.
 template <typename WT, int LPP, int MROWS, bool PANEL = false, bool LONGCTX = true>
 __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* __restrict__ vc, const AttnArgs& a,
                                            float* lds, int split, int g, int qpart = 0, int n_qparts = 1) {
@@ -269,39 +270,25 @@ __device__ __forceinline__ void attn_split(const WT* __restrict__ kc, const WT* 
         const int qi = idx / hd, dim = idx - qi * hd, m = qi / grp, hq = g * grp + (qi - m * grp);
         const int hp = hq - part_h0;   // head index inside the partial buffers
         float num = 0.f, den = 0.f;
-        if (LONGCTX || n_active <= 8) {   // every statistic and partial of this output in flight at once
-            float ms[8], ls[8], os[8];
+        float ms[8], ls[8], os[8];   // every statistic and partial of this output in flight at once
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                ms[s] = -INFINITY; ls[s] = 0.f; os[s] = 0.f;
-                if (s < n_active) {
-                    const float* ml = a.part_ml + (((size_t)s * MAX_ROWS + m) * part_H + hp) * 2;
-                    ms[s] = ld_coh(ml); ls[s] = ld_coh(ml + 1);
-                    os[s] = ld_coh(a.part_o + (((size_t)s * MAX_ROWS + m) * part_H + hp) * hd + dim);
-                }
-            }
-            float gmax = -INFINITY;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) gmax = fmaxf(gmax, ms[s]);
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                if (s < n_active) {
-                    const float w = (ms[s] > -INFINITY) ? __expf(ms[s] - gmax) : 0.f;
-                    num = fmaf(w, os[s], num);
-                    den = fmaf(w, ls[s], den);
-                }
-            }
-        } else {   // more splits, one at a time: compact, and slow (the LONGCTX instances never come here, see merge_long)
-            float gmax = -INFINITY;
-            for (int s = 0; s < n_active; ++s)
-                gmax = fmaxf(gmax, ld_coh(a.part_ml + (((size_t)s * MAX_ROWS + m) * part_H + hp) * 2));
-            for (int s = 0; s < n_active; ++s) {
+        for (int s = 0; s < 8; ++s) {
+            ms[s] = -INFINITY; ls[s] = 0.f; os[s] = 0.f;
+            if (s < n_active) {
                 const float* ml = a.part_ml + (((size_t)s * MAX_ROWS + m) * part_H + hp) * 2;
-                const float ms = ld_coh(ml), ls = ld_coh(ml + 1);
-                const float w = (ms > -INFINITY) ? __expf(ms - gmax) : 0.f;
-                const float o = ld_coh(a.part_o + (((size_t)s * MAX_ROWS + m) * part_H + hp) * hd + dim);
-                num = fmaf(w, o, num);
-                den = fmaf(w, ls, den);
+                ms[s] = ld_coh(ml); ls[s] = ld_coh(ml + 1);
+                os[s] = ld_coh(a.part_o + (((size_t)s * MAX_ROWS + m) * part_H + hp) * hd + dim);
+            }
+        }
+        float gmax = -INFINITY;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) gmax = fmaxf(gmax, ms[s]);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            if (s < n_active) {
+                const float w = (ms[s] > -INFINITY) ? __expf(ms[s] - gmax) : 0.f;
+                num = fmaf(w, os[s], num);
+                den = fmaf(w, ls[s], den);
             }
         }
         st_coh(a.att + (size_t)m * H * hd + (size_t)hq * hd + dim, num / den);
@@ -393,7 +380,7 @@ __device__ __forceinline__ void attn_merge(const AttnArgs& a, float* lds, int ld
     const int D = min(hd, ATT_MERGE_D), n_sl = hd / D, D4 = D >> 2, hq = unit / n_sl, d0 = (unit - hq * n_sl) * D;
     float* buf = lds;                        // [split of the chunk][row][D]
     float* stat = lds + ATT_MERGE_BUF;       // [row][n_active][max, sum]
-    // rows at a time: all of them unless their statistics do not fit (beyond 124000 positions with 16 rows); row 0 comes last
+    // rows at a time: all of them unless their statistics do not fit (beyond 127488 positions with 16 rows); row 0 comes last
     const int rb = min(M, max(1, (lds_floats - ATT_MERGE_BUF) / (2 * n_active)));
     for (int m_hi = M; m_hi > 0; m_hi -= rb) {
         const int m_lo = max(0, m_hi - rb), R = m_hi - m_lo;

@@ -592,8 +592,8 @@ __global__ __launch_bounds__(256) void k_pf_finish_qkv(PfGemm a) {
     }
 }
 // ---- attention of a panel: the decode kernels' attn_split on 16-row chunks.  A workgroup takes (chunk, KV head) items
-// and runs the chunk's splits one after another into a region of its own (split partials, merge counter), so that the
-// last call merges them in ascending split order exactly as the last workgroup of a KV head does in the forward kernel.
+// and runs the chunk's splits one after another into a region of its own (split partials), so that the last call merges
+// them in ascending split order, the operations and the order of the forward kernel's merge (attn_merge).
 struct PfAttn {
     const float* q;        // [P][H*hd] of the panel
     float* att;            // [P][H*hd]

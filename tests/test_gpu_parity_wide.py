@@ -464,9 +464,8 @@ def test_forward_is_bit_deterministic_over_many_launches(gpu):
 
 @pytest.mark.timeout(600)
 def test_long_context_forward_is_bit_deterministic_over_many_launches(gpu):
-    """The same at a context of 9 attention splits with grouped queries (Llama-3-8B widths, two layers): the kernel
-    instances of long contexts, whose attention deals an item's query vectors to several workgroups (72 items on the
-    grid) and merges the splits from statistics staged in LDS -- more arrivals per merge counter, more hand-overs whose
-    order could show.  3000 repetitions."""
+    """The same at a context of 9 attention splits with grouped queries (Llama-3-8B widths, two layers): an item's query
+    vectors are dealt to several workgroups (72 items on the grid), and the partials of more splits from more writers are
+    polled by the merges -- more hand-overs whose order could show.  3000 repetitions."""
     s = synth.CONFIGS["l3-8b"].with_(name="l3-8b-2layers", n_layers=2, n_skip=1)
     _repeat_forwards(gpu, s, 1100, 3000)
