@@ -19,15 +19,14 @@ using namespace sdfp;
 // The forward kernels are instantiated in the sdfp_fwd_<type>_hd<n>.hip translation units: per storage type and
 // head_dim, one for prompt chunks, one draft row, one plain decode row, and one verify kernel per row count 2..9.
 namespace sdfp {
-#define SDFP_DECL(WT, ROLE, LPP, M, SPAN, LC) extern template __global__ void k_forward<WT, ROLE, LPP, M, SPAN>(FwdArgs);
-#define SDFP_DECL_DECODE(WT, LPP, SPAN, LC)                                                                       \
-    SDFP_DECL(WT, 1, LPP, 1, SPAN, LC) SDFP_DECL(WT, 3, LPP, 1, SPAN, LC)                                          \
-    SDFP_DECL(WT, 2, LPP, 2, SPAN, LC) SDFP_DECL(WT, 2, LPP, 3, SPAN, LC) SDFP_DECL(WT, 2, LPP, 4, SPAN, LC)       \
-    SDFP_DECL(WT, 2, LPP, 5, SPAN, LC) SDFP_DECL(WT, 2, LPP, 6, SPAN, LC) SDFP_DECL(WT, 2, LPP, 7, SPAN, LC)       \
-    SDFP_DECL(WT, 2, LPP, 8, SPAN, LC) SDFP_DECL(WT, 2, LPP, 9, SPAN, LC)
-#define SDFP_DECL_HD(WT, LPP)                                                                                       \
-    SDFP_DECL(WT, 0, LPP, 0, false, true) SDFP_DECL_DECODE(WT, LPP, false, false) SDFP_DECL_DECODE(WT, LPP, true, false) \
-    SDFP_DECL_DECODE(WT, LPP, false, true) SDFP_DECL_DECODE(WT, LPP, true, true)
+#define SDFP_DECL(WT, ROLE, LPP, M, SPAN) extern template __global__ void k_forward<WT, ROLE, LPP, M, SPAN>(FwdArgs);
+#define SDFP_DECL_DECODE(WT, LPP, SPAN)                                                                   \
+    SDFP_DECL(WT, 1, LPP, 1, SPAN) SDFP_DECL(WT, 3, LPP, 1, SPAN)                                          \
+    SDFP_DECL(WT, 2, LPP, 2, SPAN) SDFP_DECL(WT, 2, LPP, 3, SPAN) SDFP_DECL(WT, 2, LPP, 4, SPAN)           \
+    SDFP_DECL(WT, 2, LPP, 5, SPAN) SDFP_DECL(WT, 2, LPP, 6, SPAN) SDFP_DECL(WT, 2, LPP, 7, SPAN)           \
+    SDFP_DECL(WT, 2, LPP, 8, SPAN) SDFP_DECL(WT, 2, LPP, 9, SPAN)
+#define SDFP_DECL_HD(WT, LPP) \
+    SDFP_DECL(WT, 0, LPP, 0, false) SDFP_DECL_DECODE(WT, LPP, false) SDFP_DECL_DECODE(WT, LPP, true)
 SDFP_DECL_HD(float, 4) SDFP_DECL_HD(float, 8) SDFP_DECL_HD(float, 16) SDFP_DECL_HD(float, 32)
 SDFP_DECL_HD(bf16_t, 4) SDFP_DECL_HD(bf16_t, 8) SDFP_DECL_HD(bf16_t, 16) SDFP_DECL_HD(bf16_t, 32)
 #undef SDFP_DECL_HD
@@ -50,8 +49,9 @@ struct Carve {   // byte offsets inside the workspace
 
 constexpr int HEAD_GRID_MAX = 1024;
 constexpr int PREFILL_ROWS = MAX_ROWS;
-// shortest prompt that goes through the matrix-matrix path by default: on the 7B shape that path takes 4.1 ms for 4 rows,
-// 4.2 (8), 4.6 (16), 5.2 (32), 6.5 (64); the 16-row forward 3.3 ms (1 row), 3.8 (4), 4.6 (6), 5.0 (8), 10.5 (16)
+// shortest prompt that goes through the matrix-matrix path by default.  7B shape, ms of that path / of the 16-row forward: 3.75 / 3.46
+// (1 row), 3.88 / 3.84 (4), 3.92 / 4.04 (5), 3.95 / 4.38 (6), 4.07 / 4.83 (8), 4.47 / 9.15 (16), 6.09 / 36.3 (64).  13B is equal at
+// 4 rows, d 2560 at 5 and 6; Llama-3-8B crosses at 7, 70B at 9 (5 rows 1.88 / 1.64 of 4 layers), small models at 8 to 13.
 constexpr int PREFILL_MATRIX_MIN_ROWS = 5;
 constexpr int TRACE_CAP = 1024;
 constexpr int LDS_DONE_MAX = 64;   // a context launches at most 3 + 2 * 8 different forward kernels and some 25 of the prompt path
@@ -759,7 +759,8 @@ int do_prefill_gemm(sd_ctx* c, int n, HeadPlan hp) {
                 a.n_nt = (a.n_tiles + 8 * nt_gu - 1) / (8 * nt_gu);
                 e = nt_gu == 3 ? launch_pf(c, k_pf_gemm<PF_GATEUP, 3, false>, gemm_grid(a), blk, PF_LDS_BYTES, a)
                                : launch_pf(c, k_pf_gemm<PF_GATEUP, 4, false, 4, 2>, gemm_grid(a), blk, PF_LDS_BYTES, a);
-            } else {   // (dealing the shares as for QKV does not pay here: 172 workgroups as it is, 72 vs 65 us on the 7B shape)
+            } else {   // (dealing the shares as for QKV did not pay here: 172 workgroups as it is, 72 vs 65 us on the 7B shape with
+                       // the pieces one slab ahead; 57 us now without)
                 a.n_nt = (a.n_tiles + 7) / 8;
                 e = SDFP_PF_ONE_TILE(PF_GATEUP, false);
             }

@@ -848,7 +848,7 @@ struct Projection {
             ld.release();
             const Turn t0 = ld.next_turn();
 #pragma unroll
-            for (int j = 0; j < RD; ++j) 
+            for (int j = 0; j < RD; ++j)
                 if (STRAIGHT || j / SPW < t0.nb) ring.r[j] = ld.load(t0, j);
         }
         // The turn that follows the one in the ring.  The loader steps ahead of its use: crossing into the next phase reads
