@@ -211,7 +211,7 @@ inline double pf_panel_us(const PfModel& m, int rows, int pos0, double gemms_us)
 // rows of the 13B shape (4 layers) as 7 + 6 tiles and not 8 + 5: 6.66 -> 6.26 ms, gate/up in 2 + 2 rounds of workgroups and not
 // 4 + 2; 1100 of the 7B shape as 2 + 8 + 8: 6.65 -> 6.28 (attention behind 8 splits costs a few rows what it costs a full panel).
 // Over 20 shapes, d 512 to 8192, and 17 lengths from 513 to 4096 no cut that is chosen was slower than full panels, those that
-// differ are 5 to 6 % quicker; without attention and the XCDs in the model the same rule lost up to 23 % (d 2560, 3500 rows).
+// differ are 7 % quicker on average, 2 to 23 %; without attention and the XCDs in the model the same rule lost up to 23 % (d 2560, 3500 rows).
 // Long prompts are cut PF_CUT_TILES row tiles at a time (the caller comes again with what is left): up to 70 us of host work, in
 // front of the first panel, and beside the GPU's from then on.
 constexpr int PF_CUT_TILES = 64;
